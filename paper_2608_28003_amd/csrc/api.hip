@@ -124,6 +124,23 @@ void tile_shape(int tile, int* bm, int* bn) {
     case TILE_GLU_128x32_K3: *bm = 128; *bn = 32; break;
     case TILE_64x64_K3: *bm = 64; *bn = 64; break;
     case TILE_256x128_W4: *bm = 256; *bn = 128; break;
+    case TILE_RING_256: *bm = 256; *bn = 256; break;
+    case TILE_RING_224: *bm = 256; *bn = 224; break;
+    case TILE_RING_192: *bm = 256; *bn = 192; break;
+    case TILE_RING_160: *bm = 256; *bn = 160; break;
+    case TILE_RING_128: *bm = 256; *bn = 128; break;
+    case TILE_KW_64x144: *bm = 64; *bn = 144; break;
+    case TILE_KW_64x96: *bm = 64; *bn = 96; break;
+    case TILE_KW_64x64: case TILE_KW_64x64_W8: *bm = 64; *bn = 64; break;
+    case TILE_KW_32x64: case TILE_KW_32x64_W8: *bm = 32; *bn = 64; break;
+    case TILE_KW_32x32: case TILE_KW_32x32_W8: *bm = 32; *bn = 32; break;
+    case TILE_KW_64x32_W8: *bm = 64; *bn = 32; break;
+    case TILE_KW_64x128: *bm = 64; *bn = 128; break;
+    case TILE_KW_128x64: *bm = 128; *bn = 64; break;
+    case TILE_KW_32x128: *bm = 32; *bn = 128; break;
+    case TILE_KW_16x64: *bm = 16; *bn = 64; break;
+    case TILE_KW_16x32: *bm = 16; *bn = 32; break;
+    case TILE_KW_16x16_W16: *bm = 16; *bn = 16; break;
     default: *bm = 128; *bn = 128;
   }
 }
@@ -207,123 +224,145 @@ bool plan_stream(Plan& p, int64_t m, int64_t n, int64_t kb, bool glu, bool f8) {
   return found;
 }
 
+// ---- cost models of the K-wave and the ring kernel, in microseconds on 256 CUs
+//
+// Both were fitted to sweeps over M = 1 ... 4096 of (N, K) = (1152, 6912),
+// (1536, 1152), (6912, 1152), (640, 2048) and (2560, 10240), and of the gated
+// pairs (d, f) = (1152, 6912), (640, 2048), (1536, 4608) and (2560, 10240); they
+// only have to rank the tiles.
+
+struct KwTile { int tile, bm, bn, waves; };
+const KwTile kKwTiles[] = {
+    {TILE_KW_16x16_W16, 16, 16, 16}, {TILE_KW_16x32, 16, 32, 8}, {TILE_KW_32x32, 32, 32, 4}, {TILE_KW_32x64, 32, 64, 4},
+    {TILE_KW_64x32_W8, 64, 32, 8}, {TILE_KW_64x64, 64, 64, 4}, {TILE_KW_64x96, 64, 96, 4},
+    {TILE_KW_64x144, 64, 144, 4}};
+const KwTile kKwGluTiles[] = {
+    {TILE_KW_16x64, 16, 64, 4}, {TILE_KW_32x64, 32, 64, 4}, {TILE_KW_64x64, 64, 64, 4},
+    {TILE_KW_64x128, 64, 128, 4}};
+
+// A CU takes ceil(tiles / 256) tiles and pulls their operands at 70 - 80 GB/s
+// (weights cold in HBM); what the waves' exchange and the epilogue cost grows
+// with the tile, and a tile whose exchange leaves room for one workgroup a CU
+// exposes its first loads.  Measured on int8 1152 x 6912 with cold weights:
+// 64 x 144 at M = 2048 25.0 us, 64 x 96 at 1024 19.7, 64 x 64 at 777 14.7,
+// 64 x 32 at 400 10.8, 32 x 32 at 128 9.7, 16 x 32 at 64 7.9, 16 x 16 at 16 6.7.  Row-major bf16
+// rows (64-byte pieces) count three times.
+double kwave_us(const KwTile& t, int64_t m, int64_t n, int64_t row_bytes, bool glu, bool a_rows) {
+  const int64_t bn = glu ? t.bn / 2 : t.bn;
+  const double per_cu = (double)ceil_div(ceil_div(m, t.bm) * ceil_div(n, bn), 256);
+  const double kib = ((a_rows ? 3.0 : 1.0) * t.bm + t.bn) * (double)row_bytes;
+  if (glu) return 4.9 + per_cu * (1.25e-5 * kib + 2.0e-4 * t.bm * t.bn);
+  const bool alone = t.waves * t.bm * t.bn * 4 > 80 * 1024;
+  return 2.6 + (alone ? 1.0 : t.waves > 8 ? 0.5 : 0.0) + per_cu * (1.4e-5 * kib + 1.2e-4 * t.bm * t.bn);
+}
+
+// A step of the ring kernel costs a fixed part and one per column block, its
+// epilogue (alone on the vector unit) as much again per block; every XCD's 32
+// CUs take its eighth of the tiles in rounds (gated int8 d = 1152, f = 6912 on
+// 256 x 128: M = 512 14.4 us; 256 x 256: M = 2048 41.8 us).
+double ring_us(int bn_rows, int64_t m, int64_t n, int64_t steps, bool glu) {
+  const int64_t bn = glu ? bn_rows / 2 : bn_rows;
+  const double blocks = bn_rows / 16.0;
+  const double rounds = (double)ceil_div(ceil_div(ceil_div(m, 256) * ceil_div(n, bn), 8), 32);
+  return 4.0 + rounds * (steps * (0.186 + 0.0337 * blocks) + (glu ? 0.31 : 0.16) * blocks);
+}
+
+// The better of the two kernels: its tile, and the model's time in *us.
+int plan_kwave_or_ring(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows, double* us) {
+  const int64_t row_bytes = dt == DT_BF16 ? 2 * k : k;
+  int best = -1;
+  double t_best = 0;
+  auto take = [&](int tile, double t) {
+    if (best < 0 || t < t_best) {
+      best = tile;
+      t_best = t;
+    }
+  };
+  const KwTile* kw = glu ? kKwGluTiles : kKwTiles;
+  const int n_kw = glu ? (int)(sizeof(kKwGluTiles) / sizeof(KwTile)) : (int)(sizeof(kKwTiles) / sizeof(KwTile));
+  for (int i = 0; i < n_kw; ++i)
+    take(kw[i].tile, kwave_us(kw[i], m, n, row_bytes, glu, a_rows && dt == DT_BF16));
+  if (dt == DT_F8) {  // a step covers two fragment columns
+    take(TILE_RING_128, ring_us(128, m, n, ceil_div(k, 2 * kFragK8) * 2, glu));
+  } else {
+    const int64_t steps = ceil_div(k, dt == DT_BF16 ? kFragK16 : kFragK8);
+    const int tiles[] = {TILE_RING_256, TILE_RING_224, TILE_RING_192, TILE_RING_160, TILE_RING_128};
+    const int rows[] = {256, 224, 192, 160, 128};
+    for (int i = 0; i < 5; ++i) take(tiles[i], ring_us(rows[i], m, n, steps, glu));
+  }
+  *us = t_best;
+  return best;
+}
+
 // Deterministic in (m, n, k, path); the workspace queries use the same plan.
-// Planner overrides for the tiled path: GEMM_TILE / GEMM_SPLITS (plain
-// epilogues) and GLU_TILE (gated epilogue).
-Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu) {
+// Planner overrides: GEMM_TILE / GEMM_SPLITS (plain epilogues) and GLU_TILE
+// (gated epilogue).  a_rows: a bf16 A operand is row-major (not packed).
+Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = true) {
   Plan p;
   p.dt = dt;
-  const bool f8 = dt == DT_F8;
+  const bool f8 = dt == DT_F8, i8 = dt == DT_I8;
   const int64_t kb = dt == DT_BF16 ? ceil_div(k, kFragK16) : ceil_div(k, kFragK8);
-  // The streaming kernel wins while the weights dominate the traffic, up to
-  // 32 rows; the tiled kernel reuses operands better beyond that (measured on
-  // the lm_head at 64 rows: 95.8 us streaming with 4 row blocks in LDS,
-  // 84.2 us on two-column 64 x 64 tiles).
+  const bool wide = ceil_div(n, 16) >= 1024 && !glu;  // the lm_head
+  // The streaming kernel: the few int8 / E4M3 rows that it quantises itself
+  // (one launch less); up to 16 rows of very wide outputs (262144 columns:
+  // M = 16 57.4 us against 62.0 on K-wave tiles, M = 32 73.8 against 67.6), of
+  // long E4M3 reductions that fit its LDS (1152 x 6912, M = 8: 6.6 against
+  // 7.7 us), and up to 32 of row-major bf16 (the same, M = 8: 10.5 against 12.9).
   if (m <= 32 && !plan_override("NO_STREAM", 0) && plan_stream(p, m, n, kb, glu, f8)) {
-    p.stream = true;
-    return p;
+    const bool fits = dt == DT_BF16 ? !glu && a_rows
+                                    : m <= 16 && (wide || m * (k / 16) <= qload_capacity(p.nw) ||
+                                                  (f8 && !glu && k >= 4096 && p.splits == 1));
+    if (fits || (wide && m <= 16)) {
+      p.stream = true;
+      return p;
+    }
   }
   p = Plan();
   p.dt = dt;
-  if (f8) {  // FP8 stages hold whole 128-deep MFMA steps: two-column tiles only
-    if (glu)  // measured: the 8-wave 256 x 64 tile from M = 512 (216 tiles) on
-      p.tile = m <= 128 ? TILE_GLU_128x32_K2
-                        : (tiles_of(TILE_GLU_256x64_K2_W8, m, n) >= 128 ? TILE_GLU_256x64_K2_W8
-                                                                       : TILE_GLU_64x64_K2);
-    else
-      p.tile = tiles_of(TILE_128x128_K2, m, n) >= 256 ? TILE_128x128_K2 : TILE_64x64_K2;
-    const int want = glu ? plan_override("GLU_TILE", p.tile) : plan_override("GEMM_TILE", p.tile);
-    if (glu ? (want == TILE_GLU_128x32_K2 || want == TILE_GLU_64x64_K2 ||
-               want == TILE_GLU_256x64_K2_W8)
-            : (want == TILE_64x64_K2 || want == TILE_128x128_K2))
-      p.tile = want;
-    const int64_t tiles = tiles_of(p.tile, m, n);
-    int64_t splits = 1;
-    if (!glu && tiles < 200)
-      splits = std::min<int64_t>(ceil_div(256, tiles), std::max<int64_t>(1, kb / 8));
-    splits = plan_override("GEMM_SPLITS", (int)splits);
-    if (glu || splits < 1) splits = 1;
-    p.kchunk = (int)round_up(ceil_div(kb, splits), 2);
-    p.splits = (int)ceil_div(kb, p.kchunk);
-    plan_order(p, m, n);
-    if (glu && plan_override("NT_OUT", -1) < 0)  // as the int8 gated plans below
-      p.nt_out = plan_override("NT_GLU", m * n * 2 >= (2 << 20) ? 1 : 0) != 0;
-    return p;
-  }
-  // int8 and bf16 choices from sweeps of the FFN shapes (d = 1152, f = 6912)
-  // and the lm_head (N = 262144) at M = 64 ... 2048
-  const bool i8 = dt == DT_I8;
-  const bool long_k = i8 && !glu && k >= 4096 && n <= 4096;  // down-projection-like
-  // bf16 (FFN shapes d = 1152, f = 6912; the FFN block, gate/up then down):
-  // the 8-wave 256 x 128 gated tile from ~200 tiles (M = 2048 242 -> 208 us,
-  // M = 1024 134 -> 119 us), the 128 x 64 gated tile from 200 tiles (M = 256
-  // 54.4 -> 50.0 us); the long-K down projection on 256 x 128 or 128 x 128
-  // tiles with three K splits from 64 tiles (M = 2048 242 -> 178 us, M = 1024
-  // 134 -> 103 us), as the int8 stack's down projection
-  const bool long_k16 = dt == DT_BF16 && !glu && k >= 4096 && n <= 4096;
-  int dflt_splits = 0;
-  if (glu) {
-    if (m <= 128)  // int8: three fragment columns a stage (M = 128: 9.95 -> 9.01 us)
-      p.tile = i8 ? TILE_GLU_128x32_K3 : TILE_GLU_128x32_K2;
-    else if (!i8 && tiles_of(TILE_GLU_256x128, m, n) >= 200)
-      p.tile = TILE_GLU_256x128;
-    else if (tiles_of(TILE_GLU_256x64, m, n) >= (i8 ? 384 : 512))  // two resident per CU
-      p.tile = TILE_GLU_256x64;
-    else if (i8)
-      p.tile = tiles_of(TILE_GLU_128x64, m, n) >= 400 ? TILE_GLU_128x64 : TILE_GLU_64x64_K2;
-    else
-      p.tile = tiles_of(TILE_GLU_128x64, m, n) >= 200 ? TILE_GLU_128x64 : TILE_GLU_64x64;
-  } else if (long_k16 && tiles_of(TILE_256x128, m, n) >= 64) {
-    p.tile = TILE_256x128;
-    dflt_splits = 3;
-  } else if (long_k16 && tiles_of(TILE_128x128, m, n) >= 64) {
-    p.tile = TILE_128x128;
-    dflt_splits = 3;
-  } else if (long_k) {
-    // with K split until ~512 workgroups are in flight (the split rule below);
-    // when the whole grid fits one workgroup per CU (the FFN down projection
-    // up to M = 128: 216 workgroups) 8 waves and stages of three fragment
-    // columns (26-layer stack at M = 128: 892 -> 844 us with 4 waves, 0.836 ->
-    // 0.825 ms with 8)
-    const int64_t t64 = tiles_of(TILE_64x64, m, n);
-    const int64_t sp = std::min<int64_t>(std::min<int64_t>(ceil_div(512, t64), 6),
-                                         std::max<int64_t>(1, kb / 8));
-    p.tile = t64 * sp <= 256 ? TILE_64x64_K3 : TILE_64x64_K2;
-  } else {
-    // measured on the lm_head (N = 262144): 256 x 256 from M = 256 (133.7 vs
-    // 162.4 us at M = 256, 888 vs 924 us at M = 2048), 128 x 128 below; from
-    // M = 512 and ~400 tiles the 4-wave 256 x 128 tile, two per CU (lm_head
-    // M = 2048 856 -> 827 us, M = 512 242 -> 237 us; N = 13824 at M = 1024
-    // 47.5 -> 40.9 us; N = 6912 at M = 2048 50.4 -> 42.9 us; with fewer tiles
-    // it loses: N = 6912 at M = 1024 36.9 vs 33.2 us)
-    if (i8 && m >= 512 && tiles_of(TILE_256x128_W4, m, n) >= 400)
-      p.tile = TILE_256x128_W4;
-    else if (m >= 256 && tiles_of(TILE_256x256, m, n) >= 512)  // bf16 lm_head: M = 2048
-      p.tile = TILE_256x256;  // 1904 -> 1419 us, M = 512 491 -> 362 us (torch 1422 / 308)
-    else if (i8 && m <= 64 && kb % 2 == 0 && tiles_of(TILE_64x64, m, n) >= 1024)
-      p.tile = TILE_64x64_K2;  // very wide outputs at up to 64 rows (lm_head)
-    else if (tiles_of(TILE_128x128, m, n) >= 256)
+  double us = 0;
+  p.tile = plan_kwave_or_ring(m, n, k, dt, glu, a_rows, &us);
+  if (wide) {
+    // 262144 columns: 32 x 64 K-wave tiles to 32 rows; to 64 rows two-column
+    // 64 x 64 tiles (int8 78.8 against 82.6 us on K-wave tiles; FP8 78.3 against
+    // 83.6), to 128 rows 128 x 128 (int8 85.2 against 107 us on the ring, bf16
+    // 160 against 167); above, the ring's widest tile (M = 256 113.9 against
+    // 128.9 us, M = 2048 661 against 822 us)
+    if (m <= 32 && dt != DT_BF16)
+      p.tile = TILE_KW_32x64;
+    else if (m <= 64 && dt != DT_BF16 && kb % 2 == 0)
+      p.tile = TILE_64x64_K2;
+    else if (m <= 128 && !f8)
       p.tile = TILE_128x128;
-    else if (tiles_of(TILE_128x64, m, n) >= 256)
-      p.tile = TILE_128x64;
-    else  // measured on the attention projections at M = 64 ... 256: the
-          // two-column stage is faster when K allows it
-      p.tile = (i8 && kb % 2 == 0) ? TILE_64x64_K2 : TILE_64x64;
+    else
+      p.tile = f8 ? TILE_RING_128 : TILE_RING_256;
+  } else if (glu && i8) {
+    // LDS tiles with two workgroups per CU (the first: one), one's epilogue
+    // over the other's products: better than the ring where the tiles fill
+    // their slots in few rounds (d = 1152, f = 6912: M = 128 8.6 against 9.1 us on
+    // K-wave tiles, M = 256 11.2 against 14.4 us, M = 1021 22.4 us both)
+    const int tiles[] = {TILE_GLU_128x32_K3, TILE_GLU_64x64_K2, TILE_GLU_128x64, TILE_GLU_256x64};
+    const double step_us[] = {0.31, 0.43, 0.65, 1.04};
+    for (int i = 0; i < 4; ++i) {
+      const int slots = i == 0 ? 256 : 512;
+      const double t = 3.0 + ceil_div(tiles_of(tiles[i], m, n), slots) * kb * step_us[i];
+      if (m > 64 && t < us) {
+        us = t;
+        p.tile = tiles[i];
+      }
+    }
   }
-  p.tile = glu ? plan_override("GLU_TILE", p.tile) : plan_override("GEMM_TILE", p.tile);
-  const int64_t tiles = tiles_of(p.tile, m, n);
-  int splits = 1;
-  if (dflt_splits > 0)
-    splits = dflt_splits;
-  else if (long_k)
-    splits = (int)std::min<int64_t>(std::min<int64_t>(ceil_div(512, tiles), 6),
-                                    std::max<int64_t>(1, kb / 8));
-  else if (!glu && tiles < 200)  // int8: at least 16 fragments per split (a split of a
-                                 // 1152-deep K costs more than the parallelism it adds)
-    splits = (int)std::min<int64_t>(ceil_div(256, tiles), std::max<int64_t>(1, kb / (i8 ? 16 : 4)));
-  splits = plan_override("GEMM_SPLITS", splits);
-  if (glu || splits < 1) splits = 1;
+  const int want = glu ? plan_override("GLU_TILE", p.tile) : plan_override("GEMM_TILE", p.tile);
+  // FP8 stages hold whole 128-deep MFMA steps: of the LDS tiles only the
+  // two-column ones exist for it
+  const bool exists = !f8 || tile_is_kwave(want) || tile_is_ring(want) ||
+                      (glu ? want == TILE_GLU_128x32_K2 || want == TILE_GLU_64x64_K2 ||
+                                 want == TILE_GLU_256x64_K2_W8
+                           : want == TILE_64x64_K2 || want == TILE_128x128_K2);
+  if (exists) p.tile = want;
+  int64_t splits = plan_override("GEMM_SPLITS", 1);
+  if (glu || splits < 1 || tile_is_kwave(p.tile) || tile_is_ring(p.tile)) splits = 1;
   p.kchunk = (int)ceil_div(kb, splits);
+  if (f8) p.kchunk = (int)round_up(p.kchunk, 2);
   p.splits = (int)ceil_div(kb, p.kchunk);
   plan_order(p, m, n);
   // the gated output h streams past the caches too, so its operand panels stay
@@ -580,28 +619,15 @@ Plan stack_down_plan(int64_t m, int64_t d, int64_t f) {
     }
     return p;
   }
-  // Large M: bigger tiles with the K range cut in three (the glue adds the
-  // partial sums), measured on the 26-layer stack (all26 + lm_head): M = 2048
-  // 4.41 -> 4.12 ms with 256 x 128 tiles, M = 1024 2.49 -> 2.45 ms with
-  // 128 x 128; from M = 512 down the plan above stays best.
-  int dflt_splits = p.splits;
-  if (tiles_of(TILE_256x128, m, d) >= 64) {
-    p.tile = TILE_256x128;
-    dflt_splits = 3;
-  } else if (tiles_of(TILE_128x128, m, d) >= 64) {
-    p.tile = TILE_128x128;
-    dflt_splits = 3;
-  }
+  // DOWN_TILE / DOWN_SPLITS: experiments with split tiles, whose partial sums
+  // the glue adds (the planner itself takes whole sums on K-wave or ring tiles)
   p.tile = plan_override("DOWN_TILE", p.tile);
+  if (tile_is_kwave(p.tile) || tile_is_ring(p.tile)) return p;
   const int64_t kb = ceil_div(f, kFragK8);
-  const int splits = std::max(1, plan_override("DOWN_SPLITS", dflt_splits));
+  const int splits = std::max(1, plan_override("DOWN_SPLITS", p.splits));
   p.kchunk = (int)ceil_div(kb, splits);
   p.splits = (int)ceil_div(kb, p.kchunk);
   plan_order(p, m, d);
-  // the int32 sums go straight to the next glue through memory: stored
-  // non-temporally they leave the operand panels in L2 (26-layer stack
-  // 1.43 -> 1.40 ms at M = 512, 2.149 -> 2.115 ms at 1024, 3.49 -> 3.46 ms at
-  // 2048)
   if (plan_override("NT_OUT", -1) < 0)
     p.nt_out = plan_override("NT_DOWN", (int64_t)p.splits * m * d * 4 >= (2 << 20) ? 1 : 0) != 0;
   return p;
@@ -1353,6 +1379,10 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
   }
   // K-split planes of each layer's down projection output
   std::vector<int> out_splits(desc->n_layers, 0);
+  // Whole sums (no K split) above one token: the down projection rounds its
+  // output y to bf16 itself, as the glue would, and the glue reads 2 bytes an
+  // element instead of 4 per split (at one token the decode paths read sums)
+  auto whole = [&](int64_t l) { return m > 1 && (prec[l] ? p8 : p16).splits == 1; };
   auto splits_of = [&](int64_t l) { return out_splits[l]; };
 
   // Glue launch l (0..n_layers): FFN output of layer l-1 into the token
@@ -1370,10 +1400,14 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
     if (hidden && l > 0) g.x_copy = hidden + (l - 1) * m * d;
     if (l > 0) {
       const bool i8 = prec[l - 1] != 0;
-      g.part = part;
-      g.splits = splits_of(l - 1);
-      g.part_f32 = !i8;
-      if (i8) {
+      if (whole(l - 1)) {
+        g.y = (const uint16_t*)part;
+      } else {
+        g.part = part;
+        g.splits = splits_of(l - 1);
+        g.part_f32 = !i8;
+      }
+      if (g.part && i8) {
         g.s_t = sh;
         g.s_i = desc->int8_ffn[l - 1].s_down;
       }
@@ -1474,18 +1508,26 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
       if (!fused(l))
         CHECK(run_gemm(pg8, DT_I8, EPI_GLU, q, 0, m, L->wq_gate, L->wq_up, f, d, s, L->s_gate,
                        L->s_up, h, f, nullptr, st));
-      if (plan_qloads(p8, m, f)) {
+      if (plan_qloads(p8, m, f) && !whole(l)) {
         CHECK(run_gemm_raw(p8, DT_I8, nullptr, 0, m, L->wq_down, d, f, part, st,
                            QLoad{h, L->delta_down, sh}));
       } else {
         CHECK(quant_act_impl(h, true, m, f, L->delta_down, qh, sh, st));
-        CHECK(run_gemm_raw(p8, DT_I8, qh, 0, m, L->wq_down, d, f, part, st));
+        if (whole(l))
+          CHECK(run_gemm(p8, DT_I8, EPI_BF16, qh, 0, m, L->wq_down, nullptr, d, f, sh, L->s_down,
+                         nullptr, part, d, nullptr, st));
+        else
+          CHECK(run_gemm_raw(p8, DT_I8, qh, 0, m, L->wq_down, d, f, part, st));
       }
     } else {
       const w8a8_bf16_ffn_desc* L = &desc->bf16_ffn[l];
       CHECK(run_gemm(pg16, DT_BF16, EPI_GLU, a, d, m, L->wp_gate, L->wp_up, f, d, nullptr, nullptr,
                      nullptr, h, f, nullptr, st));
-      CHECK(run_gemm_raw(p16, DT_BF16, h, f, m, L->wp_down, d, f, part, st));
+      if (whole(l))
+        CHECK(run_gemm(p16, DT_BF16, EPI_BF16, h, f, m, L->wp_down, nullptr, d, f, nullptr, nullptr,
+                       nullptr, part, d, nullptr, st));
+      else
+        CHECK(run_gemm_raw(p16, DT_BF16, h, f, m, L->wp_down, d, f, part, st));
     }
   }
   const int64_t V = desc->vocab, nl = desc->n_layers;

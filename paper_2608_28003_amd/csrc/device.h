@@ -108,6 +108,36 @@ __device__ __forceinline__ v4f mma_f8(v4i a0, v4i a1, v4i b0, v4i b1, v4f c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0, 0, 0);
 }
 
+// Accumulator of one 16 x 16 output block per operand type (enum DType in
+// kernels.h: 0 int8, 1 bf16, 2 E4M3).
+template <int DT>
+struct Acc;
+template <>
+struct Acc<0> {
+  typedef v4i T;
+  static __device__ __forceinline__ T zero() { return v4i{0, 0, 0, 0}; }
+  static __device__ __forceinline__ T mma(v4i a, v4i b, T c) { return mma_i8(a, b, c); }
+};
+template <>
+struct Acc<1> {
+  typedef v4f T;
+  static __device__ __forceinline__ T zero() { return v4f{0.f, 0.f, 0.f, 0.f}; }
+  static __device__ __forceinline__ T mma(v4i a, v4i b, T c) { return mma_bf16(a, b, c); }
+};
+template <>
+struct Acc<2> {
+  typedef v4f T;
+  static __device__ __forceinline__ T zero() { return v4f{0.f, 0.f, 0.f, 0.f}; }
+  // two consecutive 16 x 64 fragments of A and B: K = 128
+  static __device__ __forceinline__ T mma2(v4i a0, v4i a1, v4i b0, v4i b1, T c) {
+    return mma_f8(a0, a1, b0, b1, c);
+  }
+};
+
+// fragments consumed by one MFMA of a type
+template <int DT>
+constexpr int frags_per_mma() { return DT == 2 ? 2 : 1; }
+
 // binary32 pair -> two E4M3 codes (round to nearest even), low 16 bits
 __device__ __forceinline__ uint32_t e4m3_pack2(float lo, float hi) {
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(lo, hi, 0, false) & 0xffffu;

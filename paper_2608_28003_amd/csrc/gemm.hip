@@ -23,6 +23,8 @@
 // order and runs the epilogue.  The kernel boundary makes the partials
 // visible, so no device-scope fence (an L2 write-back + invalidate per XCD on
 // this chip) is ever issued, and the result does not depend on timing.
+#include <atomic>
+
 #include "device.h"
 #include "kernels.h"
 #include "rowquant.h"
@@ -39,34 +41,6 @@ __device__ __forceinline__ v4i load_frag_rowmajor_bf16(const void* base, int64_t
                       (lane >> 4) * 8;
   return *reinterpret_cast<const v4i*>(p);
 }
-
-template <int DT>
-struct Acc;
-template <>
-struct Acc<DT_I8> {
-  typedef v4i T;
-  static __device__ __forceinline__ T zero() { return v4i{0, 0, 0, 0}; }
-  static __device__ __forceinline__ T mma(v4i a, v4i b, T c) { return mma_i8(a, b, c); }
-};
-template <>
-struct Acc<DT_BF16> {
-  typedef v4f T;
-  static __device__ __forceinline__ T zero() { return v4f{0.f, 0.f, 0.f, 0.f}; }
-  static __device__ __forceinline__ T mma(v4i a, v4i b, T c) { return mma_bf16(a, b, c); }
-};
-template <>
-struct Acc<DT_F8> {
-  typedef v4f T;
-  static __device__ __forceinline__ T zero() { return v4f{0.f, 0.f, 0.f, 0.f}; }
-  // two consecutive 16 x 64 fragments of A and B: K = 128
-  static __device__ __forceinline__ T mma2(v4i a0, v4i a1, v4i b0, v4i b1, T c) {
-    return mma_f8(a0, a1, b0, b1, c);
-  }
-};
-
-// fragments consumed by one MFMA of a type
-template <int DT>
-constexpr int frags_per_mma() { return DT == DT_F8 ? 2 : 1; }
 
 // Dequantised / converted value of one accumulator element.
 template <int DT>
@@ -896,8 +870,22 @@ static bool gemm_params_ok(int dt, int epi, const GemmParams& p, int kind, int n
   return true;
 }
 
+int device_cus() {
+  static std::atomic<int> cached[64];  // 0: not asked yet
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+  int n = cached[dev].load(std::memory_order_relaxed);
+  if (n == 0 && hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess)
+    cached[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
+
 hipError_t launch_gemm_tile(int dt, int epi, int tile, const GemmParams& p, hipStream_t st) {
   if (!gemm_params_ok(dt, epi, p, 0)) return hipErrorInvalidValue;
+  if (tile_is_kwave(tile))
+    return p.splits == 1 ? launch_gemm_kwave(dt, epi, tile, p, st) : hipErrorInvalidValue;
+  if (tile_is_ring(tile))
+    return p.splits == 1 ? launch_gemm_ring(dt, epi, tile, p, device_cus(), st) : hipErrorInvalidValue;
   switch (dt) {
     case DT_I8: return tile_epi<DT_I8>(epi, tile, p, st);
     case DT_BF16: return tile_epi<DT_BF16>(epi, tile, p, st);

@@ -73,9 +73,9 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(const uint16_t* x,
 // optional and in this order (the arithmetic of every step is the one of the
 // standalone kernels: split-K reduction + dequant epilogue, rmsnorm_kernel,
 // quant_rows_kernel):
-//   1. y = FFN output from split-K partial sums (int32 with two scales, or
-//      fp32), rounded to bf16;  x_out = bf16(x_in + bf16(RMSNorm(y)));
-//      without partial sums x_out = x_in.
+//   1. y = FFN output, read as bf16 or formed from split-K partial sums (int32
+//      with two scales, or fp32) and rounded to bf16;  x_out = bf16(x_in + bf16(RMSNorm(y)));
+//      without an FFN output x_out = x_in.
 //   2. a = bf16(RMSNorm(x_out)), written as bf16 and/or
 //   3. smoothed by delta and quantised per row into the fragment layout
 //      (codes q, scale s); rows in [m, rows_pad) and columns in [d, kp) of
@@ -114,6 +114,7 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
   float4 si0 = make_float4(0.f, 0.f, 0.f, 0.f), si1 = si0;
   float st = 0.0f;
   int4 pr[MAXZ][2];  // int32 partial sums, or the bits of fp32 ones
+  uint4 yraw = make_uint4(0, 0, 0, 0);
   const int64_t plane = g.m * d;
   if (own) {
     xraw = *reinterpret_cast<const uint4*>(g.x_in + r * d + col0);
@@ -121,7 +122,9 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       d0 = *reinterpret_cast<const float4*>(g.delta + col0);
       d1 = *reinterpret_cast<const float4*>(g.delta + col0 + 4);
     }
-    if (g.part) {
+    if (g.y) {
+      yraw = *reinterpret_cast<const uint4*>(g.y + r * d + col0);
+    } else if (g.part) {
       const int32_t* pp = reinterpret_cast<const int32_t*>(g.part) + r * d + col0;
 #pragma unroll
       for (int z = 0; z < MAXZ; ++z)
@@ -142,11 +145,18 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       xv[2 * j + 1] = bf16_bits_to_float(w[j] >> 16);
     }
   }
-  if (g.part) {
+  if (g.part || g.y) {
     float y[8];
     float ss = 0.0f;
     if (own) {
-      if (g.part_f32) {
+      if (g.y) {
+        const uint32_t w[4] = {yraw.x, yraw.y, yraw.z, yraw.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          y[2 * j] = bf16_bits_to_float(w[j] & 0xffffu);
+          y[2 * j + 1] = bf16_bits_to_float(w[j] >> 16);
+        }
+      } else if (g.part_f32) {
         const float* pp = reinterpret_cast<const float*>(g.part) + r * d + col0;
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -201,7 +211,7 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       }
     }
   }
-  const bool write_out = g.x_out && (g.part || g.x_out != g.x_in);
+  const bool write_out = g.x_out && (g.part || g.y || g.x_out != g.x_in);
   if (own && (write_out || g.x_copy)) {
     uint4 o;
     o.x = (uint32_t)float_to_bf16_bits(xv[0]) | ((uint32_t)float_to_bf16_bits(xv[1]) << 16);

@@ -63,6 +63,9 @@ struct GemmParams {
   // far larger than the L2, e.g. the logits, so they do not evict the operands).
   int xcd_m = 0;
   int nt_out = 0;
+  // Ring and K-wave kernels, bf16: A in the packed bf16 layout; the output in it.
+  int a_packed = 0;
+  int out_packed = 0;
 };
 
 // Operand / accumulator types of the GEMM kernels (the launchers take an int;
@@ -97,6 +100,29 @@ enum TileCfg {
                                // four stages, 96 KiB of LDS (1 per CU)
   TILE_256x128_W4 = 17,        // 4 waves of 128 x 64, three stages, 72 KiB of LDS
                                // (2 per CU)
+  // K-wave kernel (gemm_kwave.hip): 4 waves, or 8 (_W8), each over the whole tile
+  TILE_KW_64x144 = 32,
+  TILE_KW_64x96 = 33,
+  TILE_KW_64x64 = 34,
+  TILE_KW_64x64_W8 = 35,
+  TILE_KW_32x64_W8 = 36,
+  TILE_KW_32x32_W8 = 37,
+  TILE_KW_64x32_W8 = 38,
+  TILE_KW_32x64 = 39,
+  TILE_KW_32x32 = 40,
+  TILE_KW_64x128 = 41,
+  TILE_KW_128x64 = 42,
+  TILE_KW_32x128 = 43,
+  TILE_KW_16x64 = 44,
+  TILE_KW_16x32 = 45,
+  TILE_KW_16x16_W16 = 46,
+  // persistent ring kernel (gemm_ring.hip): 256 rows x this many weight rows
+  // (the gated epilogue: half gate, half up)
+  TILE_RING_256 = 64,
+  TILE_RING_224 = 65,
+  TILE_RING_192 = 66,
+  TILE_RING_160 = 67,
+  TILE_RING_128 = 68,
 };
 
 hipError_t launch_col_absmax(const void* x, bool bf16, int64_t rows, int64_t k, float* amax,
@@ -118,8 +144,16 @@ hipError_t launch_geglu_requant(const float* g, const float* u, int64_t m, int64
 hipError_t launch_unpack(const void* qp, int64_t n, int64_t k, int8_t* q, hipStream_t st);
 hipError_t launch_pack_bf16(const void* w, int64_t n, int64_t k, void* wp, hipStream_t st);
 
+// compute units of the current device (0 when that cannot be asked)
+int device_cus();
 // tiled MFMA GEMM (any M); `tile` picks the block shape
 hipError_t launch_gemm_tile(int dt, int epi, int tile, const GemmParams& p, hipStream_t st);
+// the K-wave kernel (TILE_KW_*): no K splits over workgroups
+constexpr bool tile_is_kwave(int tile) { return tile >= TILE_KW_64x144 && tile <= TILE_KW_16x16_W16; }
+// the persistent ring kernel (TILE_RING_*): one workgroup on each of `cus` CUs
+constexpr bool tile_is_ring(int tile) { return tile >= TILE_RING_256 && tile <= TILE_RING_128; }
+hipError_t launch_gemm_ring(int dt, int epi, int tile, const GemmParams& p, int cus, hipStream_t st);
+hipError_t launch_gemm_kwave(int dt, int epi, int tile, const GemmParams& p, hipStream_t st);
 // streaming MFMA GEMM for M <= 128: weights streamed from HBM, A staged in
 // LDS; nw waves per workgroup, wk of them splitting one column block's K range
 // Largest M * K / 16 a streaming workgroup of nw waves can quantise on load.
@@ -143,7 +177,8 @@ struct GlueParams {
   int64_t rows_pad = 0, kp = 0;        // packed code shape (q only)
   const uint16_t* x_in = nullptr;      // token stream in, bf16 m x d
   uint16_t* x_out = nullptr;           // token stream out (may alias x_in)
-  const void* part = nullptr;          // splits x m x d partial sums, or null
+  const uint16_t* y = nullptr;         // the FFN output, bf16 m x d, or null
+  const void* part = nullptr;          // else: splits x m x d partial sums of it, or null
   int splits = 1;
   bool part_f32 = false;               // fp32 partials (bf16 layer) or int32 (INT8 layer)
   const float* s_t = nullptr;          // int32 partials: per-token scale
