@@ -1817,8 +1817,8 @@ w8a8_status w8a8_kv_quantize(const void* kv, int64_t rows, int64_t ld, int8_t* c
 }
 
 namespace {
-// workgroups the rows of a decode attention are split over (measured at 4
-// heads: 131072 rows 43.6 us with 256, 33.2 us with 512; 32768 rows equal)
+// workgroups the rows of a decode attention are split over: two a CU, and what
+// the merge loads at once
 int attn_wg_target() { return plan_override("ATTN_WGS", 512); }
 
 w8a8_status attn_common(const void* qkv, int n_heads, int64_t pos, int64_t window, int64_t t_max,

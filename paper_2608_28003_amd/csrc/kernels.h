@@ -291,7 +291,7 @@ struct AttnParams {
 hipError_t launch_kv_quant(const uint16_t* src, int64_t rows, int64_t ld, int8_t* codes,
                            float* scales, hipStream_t st);
 // target: workgroups to split the rows over (at most kAttnWgTarget)
-constexpr int kAttnWgTarget = 1024;
+constexpr int kAttnWgTarget = 512;
 hipError_t launch_attn_decode(AttnParams p, int nh, bool i8, int target, hipStream_t st);
 size_t attn_ws_bytes(int64_t rows, int target);  // workspace of one launch over `rows` rows
 size_t attn_ws_bytes_max(int64_t t_max);  // ... of any launch over at most t_max rows
