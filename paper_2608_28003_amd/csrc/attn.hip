@@ -85,9 +85,11 @@ __global__ __launch_bounds__(256) void kv_quant_kernel(const uint16_t* __restric
 // of exp(score - m), and the unnormalised output o (256 values).
 constexpr int kPartFloats = 2 * kMaxHeads + kMaxHeads * kHd;
 
-// Both products run on the matrix cores (the vector form spent 6 of its 10.5 us
-// at 32768 INT8 rows and 4 heads on products, conversions and LDS reads of the
-// query; this one takes @ATT@).  Scores: a 16-row tile of keys is the first
+// Both products run on the matrix cores: in vector instructions the products,
+// the conversions and the LDS reads of the query outlasted the loads (32768 INT8
+// rows, 4 heads: kernel 10.5 -> 8.9 us, call 16.1 -> 12.0 us; 131072 rows 30.0 ->
+// 21.9 us; bf16 17.8 -> 13.6 and 39.9 -> 35.7 us; up to 4096 rows, where the
+// launches bound it, unchanged).  Scores: a 16-row tile of keys is the first
 // operand, the query heads are the columns of the second, both read straight
 // from memory (any assignment of the 256 dimensions to the K positions serves,
 // so a lane's 16-byte pieces are what is contiguous in a row; codes become bf16
@@ -375,7 +377,7 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
 // Merge of at most 32 * CPT partial results: eight workgroups a head, each over
 // 32 output dimensions with 32 groups of threads, group j taking the chunks j,
 // j + 32, ...  Every partial's maximum, sum and output value is loaded at once
-// (one memory round trip: @MRG@), then come the maximum over the chunks, each
+// (one memory round trip: 256 partials of 4 heads 6.1 -> 4.0 us), then come the maximum over the chunks, each
 // thread's factors exp(m_c - M), and the sums over the waves in wave order.
 template <int CPT>
 __global__ __launch_bounds__(1024) void attn_merge_kernel(AttnParams p) {
