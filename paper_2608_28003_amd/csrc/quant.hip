@@ -13,6 +13,8 @@
 // the row absmax, and each chunk becomes one 16-byte (8-byte) store into its
 // fragment slot.  All arithmetic is IEEE binary32 (correctly rounded division,
 // v_rndne_f32 for round-half-to-even, no contraction).
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -101,6 +103,62 @@ __global__ __launch_bounds__(256) void col_absmax_kernel(const T* __restrict__ x
   }
   // non-negative binary32 values order like their unsigned bit patterns
   atomicMax(reinterpret_cast<unsigned int*>(amax) + j, __float_as_uint(m));
+}
+
+// The same for k % 8 == 0 (rows on 16-byte boundaries), bound by the read of x.
+// A workgroup covers tc chunks of 8 columns (blockIdx.y: which ones) and
+// rp = 512 / tc rows at a time of its range, so it reads one contiguous piece of
+// memory; a thread keeps its chunk's 8 maxima over every row it meets, eight
+// rows of loads in flight.  The workgroup's maxima meet in LDS and reach memory
+// only where they raise it (a stale value there is lower, never higher).
+// 262144 x 1152 bf16 (604 MB): 326 -> 117 us.
+constexpr int kColThreads = 512, kColUnroll = 8;
+
+template <typename T>
+__global__ __launch_bounds__(kColThreads) void col_absmax_wide_kernel(const T* __restrict__ x,
+                                                                      int64_t rows, int64_t k, int tc,
+                                                                      int64_t rows_wg,
+                                                                      float* __restrict__ amax) {
+  __shared__ float red[kColThreads * 8];
+  const int t = threadIdx.x;
+  const int rp = kColThreads / tc, rr = t / tc;
+  const int64_t chunk0 = (int64_t)blockIdx.y * tc;
+  const int64_t c = chunk0 + t % tc;
+  const int64_t end = min(rows, (blockIdx.x + 1) * rows_wg);
+  float m[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) m[e] = 0.0f;
+  if (rr < rp && c < k / 8) {
+    const T* p = x + c * 8;
+    int64_t r = blockIdx.x * rows_wg + rr;
+    for (; r + (kColUnroll - 1) * rp < end; r += kColUnroll * rp) {
+      float v[kColUnroll][8];
+#pragma unroll
+      for (int i = 0; i < kColUnroll; ++i) load8<T>(p + (r + i * rp) * k, v[i]);
+#pragma unroll
+      for (int i = 0; i < kColUnroll; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m[e] = fmaxf(m[e], fabsf(v[i][e]));
+    }
+    for (; r < end; r += rp) {
+      float v[8];
+      load8<T>(p + r * k, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) m[e] = fmaxf(m[e], fabsf(v[e]));
+    }
+  }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) red[e * kColThreads + t] = m[e];
+  __syncthreads();
+  for (int i = t; i < tc * 8; i += kColThreads) {
+    const int e = i / tc, ct = i % tc;
+    if (chunk0 + ct >= k / 8) continue;
+    float v = red[e * kColThreads + ct];
+    for (int q = 1; q < rp; ++q) v = fmaxf(v, red[e * kColThreads + q * tc + ct]);
+    unsigned int* dst = reinterpret_cast<unsigned int*>(amax) + (chunk0 + ct) * 8 + e;
+    if (__float_as_uint(v) > __hip_atomic_load(dst, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(dst, __float_as_uint(v));
+  }
 }
 
 __global__ void smooth_delta_kernel(const float* __restrict__ a, const float* __restrict__ w,
@@ -303,8 +361,11 @@ __device__ __forceinline__ float div_via_f64(float a, double rb) {
 // maximum is at least 2^-118, such an element is not the maximum (its value is
 // below 2^-126 on either route) and its code is 0 on either route (|v / s| <=
 // 127 * 2^-126 / 2^-118 < 1/2); a row below 2^-118 is redone with IEEE
-// divisions.
-template <int R>
+// divisions.  E4M3 codes (F8) are 0 up to 2^-10: there the line is 2^-107
+// (448 * 2^-126 / 2^-107 < 2^-10), and the code's sign bit is the quotient's
+// on either route.  1500 x 6912 to E4M3: 17.1 us on quant_rows_kernel, 14.2
+// here; 1500 x 1152 7.1 and 6.7.
+template <int R, bool F8>
 __global__ __launch_bounds__(1024) void quant_rows_bf16_kernel(
     const uint16_t* __restrict__ x, int64_t rows, int64_t k, const float* __restrict__ delta,
     int64_t rows_pad, int64_t kp, int8_t* __restrict__ q, float* __restrict__ s) {
@@ -361,10 +422,10 @@ __global__ __launch_bounds__(1024) void quant_rows_bf16_kernel(
     for (int w = 1; w < nw; ++w) m = fmaxf(m, red[i][w]);
     mx[i] = m;
   }
-  // rows below 2^-118 (every thread holds the same maximum: a uniform branch)
+  // rows below the line (every thread holds the same maximum: a uniform branch)
 #pragma unroll
   for (int i = 0; i < R; ++i) {
-    if (!delta || r0 + i >= rows || !(mx[i] < 0x1p-118f)) continue;
+    if (!delta || r0 + i >= rows || !(mx[i] < (F8 ? 0x1p-107f : 0x1p-118f))) continue;
     float m = 0.0f;
     if (own) {  // the row is read again (the registers holding it are free by now)
       float d[16];
@@ -392,19 +453,124 @@ __global__ __launch_bounds__(1024) void quant_rows_bf16_kernel(
     if (r >= rows_pad) break;
     int32_t packed[4] = {0, 0, 0, 0};
     if (r < rows) {
-      const float sr = mx[i] / 127.0f;
+      const float sr = mx[i] / (F8 ? 448.0f : 127.0f);
       if (t == 0) s[r] = sr;
       if (own && sr != 0.0f) {
         const double rs = 1.0 / (double)sr;
+        if constexpr (F8) {  // past 448 the conversion gives NaN, see quant_rows_kernel
+#pragma unroll
+          for (int e = 0; e < 16; e += 2) {
+            const float q0 = fminf(fmaxf(div_via_f64(v[i][e], rs), -448.0f), 448.0f);
+            const float q1 = fminf(fmaxf(div_via_f64(v[i][e + 1], rs), -448.0f), 448.0f);
+            packed[e >> 2] |= (int32_t)(e4m3_pack2(q0, q1) << (8 * (e & 3)));
+          }
+        } else {
+          uint32_t b[16];
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            // |v / s| <= 127 (1 + 2^-23) except for a subnormal scale; clamping
+            // before rounding gives the codes of rounding first, as in code_of.
+            // c + 1.5 * 2^23 rounds c to an integer, ties to even (the offset is
+            // even), and its low byte is that integer in two's complement.
+            const float c = fminf(fmaxf(div_via_f64(v[i][e], rs), -127.0f), 127.0f);
+            b[e] = __float_as_uint(c + 12582912.0f);
+          }
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            packed[j] = (int32_t)((b[4 * j] & 0xffu) | ((b[4 * j + 1] & 0xffu) << 8) |
+                                  ((b[4 * j + 2] & 0xffu) << 16) | (b[4 * j + 3] << 24));
+        }
+      }
+    }
+    // blockDim covers chunks_pad: one chunk per thread (padding columns and
+    // padding rows get zero codes)
+    if (t < chunks_pad) store_codes<16>(q, r, t, kb_count, packed);
+  }
+}
+
+// ------------------------------------------------------------------ weights
+
+// Weight codes in tiles of the packed layout, bound by the read of W and the
+// write of its codes: a workgroup takes ROWS rows, a wave (64 / ROWS) 16-column
+// chunks of all of them at a time (NU such units, one load each way in flight
+// per row and chunk), and lane l holds chunk l / ROWS of row l % ROWS, so a
+// wave's store is ROWS * 16 contiguous bytes of every fragment column it meets
+// (a whole fragment at ROWS = 16) where quant_rows_kernel's are 16-byte pieces
+// of 64 fragments.  The values stay in registers between the row maxima (over
+// the lanes of a row by shuffles, over the waves through LDS) and the codes;
+// v / s through binary64, see div_via_f64: |v / s| below the normal range is
+// code 0 on either route.  Same codes and scales as quant_rows_kernel.
+// 262144 x 1152 bf16: 389 -> 200 - 214 us (4.4 TB/s); 40000 x 6912 with its column
+// maximum 572 -> 307 us.
+constexpr int kWqUnits = 3, kWqWaves = 16;
+
+template <typename T, bool F8, int ROWS>
+__global__ __launch_bounds__(64 * kWqWaves) void quant_weights_kernel(
+    const T* __restrict__ w, int64_t rows, int64_t k, const float* __restrict__ delta, int64_t kp,
+    int8_t* __restrict__ q, float* __restrict__ s) {
+  constexpr int NC = 64 / ROWS;  // chunks of a unit
+  __shared__ float red[kWqWaves][ROWS];
+  const int lane = lane_id(), wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  const int64_t r = (int64_t)blockIdx.x * ROWS + lane % ROWS;
+  const int64_t chunks = k / 16, chunks_pad = kp / 16;
+  const T* row = w + r * k;
+
+  float v[kWqUnits][16];
+  float amax = 0.0f;
+#pragma unroll
+  for (int i = 0; i < kWqUnits; ++i) {
+    const int64_t c = (int64_t)(wave + i * nw) * NC + lane / ROWS;
+    if (c < chunks && r < rows) {
+      load16<T>(row + c * 16, v[i]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[i][e] = 0.0f;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < kWqUnits; ++i) {
+    const int64_t c = (int64_t)(wave + i * nw) * NC + lane / ROWS;
+    if (delta) {
+      float d[16];
+      load16<float>(delta + min(c, chunks - 1) * 16, d);
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[i][e] = v[i][e] * d[e];
+    }
+    if (c < chunks && r < rows) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(v[i][e]));
+    }
+  }
+  if constexpr (ROWS <= 4) amax = fmaxf(amax, lane_xor<4>(amax));
+  if constexpr (ROWS <= 8) amax = fmaxf(amax, lane_xor<8>(amax));
+  amax = fmaxf(amax, lane_xor<16>(amax));
+  amax = fmaxf(amax, lane_xor<32>(amax));
+  if (lane < ROWS) red[wave][lane] = amax;
+  __syncthreads();
+  amax = red[0][lane % ROWS];
+  for (int i = 1; i < nw; ++i) amax = fmaxf(amax, red[i][lane % ROWS]);
+  const float sr = amax / (F8 ? 448.0f : 127.0f);
+  if (wave == 0 && lane < ROWS && r < rows) s[r] = sr;
+  const double rs = 1.0 / (double)sr;
+
+#pragma unroll
+  for (int i = 0; i < kWqUnits; ++i) {
+    const int64_t c = (int64_t)(wave + i * nw) * NC + lane / ROWS;
+    int32_t packed[4] = {0, 0, 0, 0};
+    if (c < chunks && r < rows && sr != 0.0f) {
+      if constexpr (F8) {
+#pragma unroll
+        for (int e = 0; e < 16; e += 2) {
+          const float q0 = fminf(fmaxf(div_via_f64(v[i][e], rs), -448.0f), 448.0f);
+          const float q1 = fminf(fmaxf(div_via_f64(v[i][e + 1], rs), -448.0f), 448.0f);
+          packed[e >> 2] |= (int32_t)(e4m3_pack2(q0, q1) << (8 * (e & 3)));
+        }
+      } else {
         uint32_t b[16];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          // |v / s| <= 127 (1 + 2^-23) except for a subnormal scale; clamping
-          // before rounding gives the codes of rounding first, as in code_of.
-          // c + 1.5 * 2^23 rounds c to an integer, ties to even (the offset is
-          // even), and its low byte is that integer in two's complement.
-          const float c = fminf(fmaxf(div_via_f64(v[i][e], rs), -127.0f), 127.0f);
-          b[e] = __float_as_uint(c + 12582912.0f);
+        for (int e = 0; e < 16; ++e) {  // rounded and packed as in quant_rows_bf16_kernel
+          const float cq = fminf(fmaxf(div_via_f64(v[i][e], rs), -127.0f), 127.0f);
+          b[e] = __float_as_uint(cq + 12582912.0f);
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
@@ -412,9 +578,8 @@ __global__ __launch_bounds__(1024) void quant_rows_bf16_kernel(
                                 ((b[4 * j + 2] & 0xffu) << 16) | (b[4 * j + 3] << 24));
       }
     }
-    // blockDim covers chunks_pad: one chunk per thread (padding columns and
-    // padding rows get zero codes)
-    if (t < chunks_pad) store_codes<16>(q, r, t, kb_count, packed);
+    // every chunk of the padded matrix has a lane (rows_pad is a multiple of ROWS)
+    if (c < chunks_pad) store_codes<16>(q, r, c, kp / kFragK8, packed);
   }
 }
 
@@ -451,6 +616,25 @@ __global__ void pack_bf16_kernel(const uint16_t* __restrict__ w, int64_t n, int6
 
 hipError_t launch_col_absmax(const void* x, bool bf16, int64_t rows, int64_t k, float* amax,
                              hipStream_t st) {
+  if (k % 8 == 0) {
+    // column tiles of about 40 chunks; about two workgroups a CU, each over a
+    // contiguous range of rows with at least one unrolled step.  Each ends with an
+    // atomic per column, and those of all workgroups meet in a few lines, so the
+    // tiles are narrow: on tiles of 216 chunks 1152 x 6912 took 28 us more than
+    // on col_absmax_kernel, 500 000 atomics against 124 000.
+    const int64_t chunks = k / 8, tiles = (chunks + 39) / 40, tc = (chunks + tiles - 1) / tiles;
+    const int64_t unit = kColThreads / tc * kColUnroll, steps = (rows + unit - 1) / unit;
+    const int64_t wgs = std::min<int64_t>(steps, std::max<int64_t>(1, 512 / tiles));
+    const int64_t rows_wg = (steps + wgs - 1) / wgs * unit;
+    dim3 grid((unsigned)((rows + rows_wg - 1) / rows_wg), (unsigned)tiles);
+    if (tiles <= 65535) {
+      if (bf16)
+        col_absmax_wide_kernel<uint16_t><<<grid, kColThreads, 0, st>>>((const uint16_t*)x, rows, k, (int)tc, rows_wg, amax);
+      else
+        col_absmax_wide_kernel<float><<<grid, kColThreads, 0, st>>>((const float*)x, rows, k, (int)tc, rows_wg, amax);
+      return hipGetLastError();
+    }
+  }
   const int rpb = 64;
   dim3 grid((unsigned)((k + 255) / 256), (unsigned)((rows + rpb - 1) / rpb));
   if (bf16)
@@ -505,7 +689,7 @@ hipError_t launch_quant_rows(const void* x, bool bf16, bool mul, int64_t rows, i
   // 8-column chunks while the rows leave CUs idle (one workgroup per row) and a
   // row still fits one workgroup
   const bool narrow = rows_pad <= 256 && kp / 8 <= 1024;
-  if (bf16 && !mul && !f8 && !narrow && kp / 16 <= 1024) {
+  if (bf16 && !mul && !narrow && kp / 16 <= 1024) {
     // many bf16 rows (activations): several rows per workgroup
     const int64_t threads = (kp / 16 + 63) / 64 * 64;
     // rows per workgroup, measured at k = 6912 (requantisation of h): 4 from
@@ -513,14 +697,44 @@ hipError_t launch_quant_rows(const void* x, bool bf16, bool mul, int64_t rows, i
     // 11.2 us; 1024 rows: 11.7 against 12.5 us); at k = 1152, 2048 rows: 7.4
     // against 10.0 us
     const int r = quant_rows_per_workgroup(rows_pad >= 2048 && kp >= 4096 ? 4 : 2);
-#define W8A8_QROWS(R)                                                                      \
-  quant_rows_bf16_kernel<R><<<(unsigned)((rows_pad + R - 1) / R), (unsigned)threads, 0, st>>>( \
+#define W8A8_QROWS(R, F8)                                                                  \
+  quant_rows_bf16_kernel<R, F8><<<(unsigned)((rows_pad + R - 1) / R), (unsigned)threads, 0, st>>>( \
       (const uint16_t*)x, rows, k, delta, rows_pad, kp, qpacked, s)
-    if (r == 1) W8A8_QROWS(1);
-    else if (r == 2) W8A8_QROWS(2);
-    else if (r == 8) W8A8_QROWS(8);
-    else W8A8_QROWS(4);
+    if (f8) {
+      if (r == 1) W8A8_QROWS(1, true);
+      else if (r == 2) W8A8_QROWS(2, true);
+      else if (r == 8) W8A8_QROWS(8, true);
+      else W8A8_QROWS(4, true);
+    } else {
+      if (r == 1) W8A8_QROWS(1, false);
+      else if (r == 2) W8A8_QROWS(2, false);
+      else if (r == 8) W8A8_QROWS(8, false);
+      else W8A8_QROWS(4, false);
+    }
 #undef W8A8_QROWS
+    return hipGetLastError();
+  }
+  if (mul && kp <= (int64_t)kWqWaves * kWqUnits * 256) {
+    // rows a workgroup: 16 store whole fragments; fewer where the row is long
+    // (a workgroup of more than 8 waves holds the chip's slots in step) or the
+    // rows are few (512 workgroups fill the chip)
+    auto units = [&](int64_t rr) { return (kp + 1024 / rr - 1) / (1024 / rr); };
+    int64_t rr = 16;
+    while (rr > 4 && (units(rr) > 8 * kWqUnits || rows_pad / rr < 512)) rr /= 2;
+    const unsigned blocks = (unsigned)(rows_pad / rr);
+    const unsigned threads = (unsigned)((units(rr) + kWqUnits - 1) / kWqUnits) * 64;
+#define W8A8_QW(T, F8, R)                                                                        \
+  quant_weights_kernel<T, F8, R><<<blocks, threads, 0, st>>>((const T*)x, rows, k, delta, kp, qpacked, s)
+#define W8A8_QW_R(T, F8)           \
+  if (rr == 16) W8A8_QW(T, F8, 16); \
+  else if (rr == 8) W8A8_QW(T, F8, 8); \
+  else W8A8_QW(T, F8, 4)
+    if (bf16 && f8) { W8A8_QW_R(uint16_t, true); }
+    else if (bf16) { W8A8_QW_R(uint16_t, false); }
+    else if (f8) { W8A8_QW_R(float, true); }
+    else { W8A8_QW_R(float, false); }
+#undef W8A8_QW_R
+#undef W8A8_QW
     return hipGetLastError();
   }
   int64_t threads = (kp / (narrow ? 8 : 16) + 63) / 64 * 64;
