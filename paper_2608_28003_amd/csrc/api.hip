@@ -407,8 +407,11 @@ bool plan_qloads(const Plan& pl, int64_t m, int64_t k) {
 w8a8_status run_gemm(const Plan& pl, int dt, int epi, const void* A, int64_t lda, int64_t m,
                      const void* B, const void* B2, int64_t n, int64_t k, const float* s_a,
                      const float* s_b, const float* s_b2, void* out, int64_t ldo, void* gemm_ws,
-                     hipStream_t st, QLoad ql = QLoad()) {
+                     hipStream_t st, QLoad ql = QLoad(), bool a_packed = false,
+                     bool out_packed = false) {
   GemmParams p{};
+  p.a_packed = a_packed ? 1 : 0;
+  p.out_packed = out_packed ? 1 : 0;
   p.a_x = ql.x;
   p.a_delta = ql.delta;
   p.a_ld = k;
@@ -575,14 +578,26 @@ FfnWs ffn_ws(int64_t m, int64_t d, int64_t f, int dt = DT_I8) {
   return w;
 }
 
+// A bf16 activation between two kernels in the packed layout: a GEMM then
+// fetches 1 KiB of consecutive memory for a fragment instead of 16 pieces of
+// 64 bytes, and needs both its kernels to be K-wave or ring (the LDS tiles and
+// the streaming kernel, which takes up to 32 rows, read rows).
+// Down projection of 1152 x 6912 at M = 1021 39.9 -> 26.2 us; in the stack at
+// M = 512 gate/up 30.4 -> 22.6 us and down 36.8 -> 30.2 us.
+bool packs(const Plan& p) { return !p.stream && (tile_is_kwave(p.tile) || tile_is_ring(p.tile)); }
+bool bf16_h_packed(int64_t m, int64_t d, int64_t f) {
+  return m > 32 && f % kFragK16 == 0 && packs(plan_gemm(m, f, d, DT_BF16, true)) &&
+         packs(plan_gemm(m, d, f, DT_BF16, false, false));
+}
+
 struct Bf16FfnWs {
   size_t h, gemm_gu, gemm_dn, total;
 };
-Bf16FfnWs bf16_ffn_ws(int64_t m, int64_t d, int64_t f) {
+Bf16FfnWs bf16_ffn_ws(int64_t m, int64_t d, int64_t f, bool packed) {
   Bf16FfnWs w;
-  Plan pd = plan_gemm(m, d, f, DT_BF16, false);
+  Plan pd = plan_gemm(m, d, f, DT_BF16, false, !packed);
   w.h = 0;
-  w.gemm_dn = align256((size_t)m * f * 2);
+  w.gemm_dn = align256(packed ? w8a8_packed_bf16_bytes(m, f) : (size_t)m * f * 2);
   w.total = w.gemm_dn + plan_ws_bytes(pd, m, d);
   w.gemm_gu = 0;
   return w;
@@ -639,6 +654,7 @@ struct StackWs {
 StackWs stack_ws(int64_t m, int64_t d, int64_t f, int64_t vocab) {
   StackWs w;
   const Plan p8 = stack_down_plan(m, d, f), p16 = plan_gemm(m, d, f, DT_BF16, false);
+  // (a packed bf16 operand's plan is a K-wave or ring tile: one split)
   // at one token the persistent decode kernel may write up to kGlueMaxSplits planes
   const int planes = std::max({p8.splits, p16.splits, m == 1 ? kGlueMaxSplits : 1});
   const size_t part = (size_t)planes * m * d * 4;
@@ -722,15 +738,18 @@ w8a8_status bf16_linear_impl(const void* x, int64_t m, const void* wp, int64_t n
 }
 
 w8a8_status bf16_ffn_impl(const w8a8_bf16_ffn_desc* d, const void* x, int64_t m, void* y,
-                          void* ws, hipStream_t st) {
-  Bf16FfnWs w = bf16_ffn_ws(m, d->d, d->f);
+                          void* ws, size_t ws_bytes, hipStream_t st) {
+  // whole fragments of h need up to 15 more rows than its m: a workspace of the
+  // plain size keeps h in rows
+  const bool packed = bf16_h_packed(m, d->d, d->f) && ws_bytes >= bf16_ffn_ws(m, d->d, d->f, true).total;
+  Bf16FfnWs w = bf16_ffn_ws(m, d->d, d->f, packed);
   char* base = (char*)ws;
   Plan pg = plan_gemm(m, d->f, d->d, DT_BF16, true);
   CHECK(run_gemm(pg, DT_BF16, EPI_GLU, x, d->d, m, d->wp_gate, d->wp_up, d->f, d->d, nullptr, nullptr,
-                 nullptr, base + w.h, d->f, nullptr, st));
-  Plan pd = plan_gemm(m, d->d, d->f, DT_BF16, false);
+                 nullptr, base + w.h, d->f, nullptr, st, QLoad(), false, packed));
+  Plan pd = plan_gemm(m, d->d, d->f, DT_BF16, false, !packed);
   return run_gemm(pd, DT_BF16, EPI_BF16, base + w.h, d->f, m, d->wp_down, nullptr, d->d, d->f,
-                  nullptr, nullptr, nullptr, y, d->d, base + w.gemm_dn, st);
+                  nullptr, nullptr, nullptr, y, d->d, base + w.gemm_dn, st, QLoad(), packed);
 }
 
 }  // namespace
@@ -761,7 +780,8 @@ size_t w8a8_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
 
 size_t w8a8_bf16_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
   if (m < 1 || d < 1 || f < 1) return 0;
-  return bf16_ffn_ws(m, d, f).total;
+  const size_t rows = bf16_ffn_ws(m, d, f, false).total;
+  return bf16_h_packed(m, d, f) ? std::max(rows, bf16_ffn_ws(m, d, f, true).total) : rows;
 }
 
 size_t w8a8_bf16_linear_workspace_bytes(int64_t m, int64_t n, int64_t k) {
@@ -1249,9 +1269,9 @@ w8a8_status w8a8_bf16_ffn(const w8a8_bf16_ffn_desc* desc, const void* x, int64_t
   CHECK_PTR(y);
   CHECK_PTR(ws);
   REQUIRE(m >= 1, W8A8_EINVAL, "m < 1");
-  REQUIRE(ws_bytes >= w8a8_bf16_ffn_workspace_bytes(m, desc->d, desc->f), W8A8_EWORKSPACE,
+  REQUIRE(ws_bytes >= bf16_ffn_ws(m, desc->d, desc->f, false).total, W8A8_EWORKSPACE,
           "workspace too small");
-  return bf16_ffn_impl(desc, x, m, y, ws, S(stream));
+  return bf16_ffn_impl(desc, x, m, y, ws, ws_bytes, S(stream));
 }
 
 // ---------------------------------------------------------------- a8 / a9
@@ -1362,8 +1382,13 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
   int8_t* qh = (int8_t*)(base + w.qh);
   float* sh = (float*)(base + w.sh);
   void* part = base + w.part;
-  const Plan p8 = stack_down_plan(m, d, f), p16 = plan_gemm(m, d, f, DT_BF16, false);
-  const Plan pg8 = plan_gemm(m, f, d, DT_I8, true), pg16 = plan_gemm(m, f, d, DT_BF16, true);
+  // bf16 layers: the block input a and h in the packed layout (beyond m rows
+  // they reach into the code regions behind them, q and qh, which a bf16 layer
+  // does not use and which from 32 rows on are larger than the 15 rows)
+  const bool packed = bf16_h_packed(m, d, f) && d % kFragK16 == 0 &&
+                      packs(plan_gemm(m, f, d, DT_BF16, true, false));
+  const Plan p8 = stack_down_plan(m, d, f), p16 = plan_gemm(m, d, f, DT_BF16, false, !packed);
+  const Plan pg8 = plan_gemm(m, f, d, DT_I8, true), pg16 = plan_gemm(m, f, d, DT_BF16, true, !packed);
   // every call starts with a clear failure word (w8a8_ffn_stack_status)
   CHECK(hip_check(launch_dec_status_clear((DecCtl*)(base + w.ctl), st), "status clear"));
 
@@ -1419,6 +1444,7 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
       g.delta = l < desc->n_layers ? desc->int8_ffn[l].delta_gu : desc->lm_head_int8.delta;
     } else {
       g.a = a;
+      g.a_packed = packed && l < desc->n_layers;  // the lm_head reads rows
     }
     CHECK(hip_check(launch_glue(g, st), "glue"));
     xin = xbuf[nxt];
@@ -1522,10 +1548,10 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
     } else {
       const w8a8_bf16_ffn_desc* L = &desc->bf16_ffn[l];
       CHECK(run_gemm(pg16, DT_BF16, EPI_GLU, a, d, m, L->wp_gate, L->wp_up, f, d, nullptr, nullptr,
-                     nullptr, h, f, nullptr, st));
+                     nullptr, h, f, nullptr, st, QLoad(), packed, packed));
       if (whole(l))
         CHECK(run_gemm(p16, DT_BF16, EPI_BF16, h, f, m, L->wp_down, nullptr, d, f, nullptr, nullptr,
-                       nullptr, part, d, nullptr, st));
+                       nullptr, part, d, nullptr, st, QLoad(), packed));
       else
         CHECK(run_gemm_raw(p16, DT_BF16, h, f, m, L->wp_down, d, f, part, st));
     }

@@ -239,7 +239,11 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       o.y = (uint32_t)float_to_bf16_bits(a[2]) | ((uint32_t)float_to_bf16_bits(a[3]) << 16);
       o.z = (uint32_t)float_to_bf16_bits(a[4]) | ((uint32_t)float_to_bf16_bits(a[5]) << 16);
       o.w = (uint32_t)float_to_bf16_bits(a[6]) | ((uint32_t)float_to_bf16_bits(a[7]) << 16);
-      *reinterpret_cast<uint4*>(g.a + r * d + col0) = o;
+      // packed: 8 columns are one lane's 16 bytes of a fragment
+      const int64_t at = g.a_packed ? (frag_offset(r >> 4, col0 / kFragK16, d / kFragK16) +
+                                       ((r & 15) + 16 * ((col0 % kFragK16) / 8)) * 16) / 2
+                                    : r * d + col0;
+      *reinterpret_cast<uint4*>(g.a + at) = o;
     }
   }
   if (!g.q) return;

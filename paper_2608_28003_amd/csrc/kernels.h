@@ -184,6 +184,7 @@ struct GlueParams {
   const float* s_t = nullptr;          // int32 partials: per-token scale
   const float* s_i = nullptr;          //                 per-column scale
   uint16_t* a = nullptr;               // pre-norm output, bf16 m x d (optional)
+  bool a_packed = false;               // ... in the packed bf16 layout (d % 32 == 0)
   const float* delta = nullptr;        // smoothing of the INT8 consumer (may be null)
   int8_t* q = nullptr;                 // packed codes of the pre-norm output (optional)
   float* s = nullptr;                  // their per-row scales

@@ -124,3 +124,22 @@ def test_gated_float_tiles(dt):
         force("GLU_TILE", tile)
         h = call().double()
         assert float((h - ref).norm() / ref.norm()) <= 2.0 ** -8, tile
+
+
+@pytest.mark.parametrize("m,d,f", [(33, 64, 96), (77, 1152, 6912), (300, 640, 2048), (1021, 1152, 6912)])
+def test_bf16_block_packed_activations(m, d, f):
+    """h in whole packed fragments (rows past m uninitialised) against h in rows,
+    which a workspace of the plain size keeps: one K-wave or ring kernel each way,
+    sums in another order, so within a bf16 rounding of h and of the output."""
+    print("bf16 block", m, d, f, flush=True)
+    cfg = synth.ffn_config(m=m, d=d, f=f)
+    layer = w8a8.FfnBF16.from_weights(*(dev_bf16(cfg[n]) for n in ("w_gate", "w_up", "w_down")))
+    x = dev_bf16(cfg["x"])
+    need, plain = w8a8.bf16_ffn_workspace_bytes(m, d, f), m * f * 2
+    assert need >= -(-m // 16) * 16 * f * 2
+    y, y_rows = (w8a8.bf16_ffn(layer, x, ws=torch.full((n,), 255, dtype=torch.uint8, device=DEV)).double()
+                 for n in (need, (plain + 255) // 256 * 256))
+    h = w8a8.bf16_ffn_gate_up(layer, x).double()
+    ref = h @ torch.from_numpy(cfg["w_down"].astype(np.uint32) << 16).to(torch.int32).view(torch.float32).to(DEV).double().t()
+    for name, got in (("packed", y), ("rows", y_rows)):
+        assert float((got - ref).norm() / ref.norm()) <= 2.0 ** -8, name
