@@ -247,10 +247,11 @@ const KwTile kKwGluTiles[] = {
 // 64 x 144 at M = 2048 25.0 us, 64 x 96 at 1024 19.7, 64 x 64 at 777 14.7,
 // 64 x 32 at 400 10.8, 32 x 32 at 128 9.7, 16 x 32 at 64 7.9, 16 x 16 at 16 6.7.  Row-major bf16
 // rows (64-byte pieces) count three times.
-double kwave_us(const KwTile& t, int64_t m, int64_t n, int64_t row_bytes, bool glu, bool a_rows) {
+double kwave_us(const KwTile& t, int64_t m, int64_t n, int64_t row_bytes, bool glu, bool a_rows,
+                int splits = 1) {
   const int64_t bn = glu ? t.bn / 2 : t.bn;
-  const double per_cu = (double)ceil_div(ceil_div(m, t.bm) * ceil_div(n, bn), 256);
-  const double kib = ((a_rows ? 3.0 : 1.0) * t.bm + t.bn) * (double)row_bytes;
+  const double per_cu = (double)ceil_div(ceil_div(m, t.bm) * ceil_div(n, bn) * splits, 256);
+  const double kib = ((a_rows ? 3.0 : 1.0) * t.bm + t.bn) * (double)row_bytes / splits;
   if (glu) return 4.9 + per_cu * (1.25e-5 * kib + 2.0e-4 * t.bm * t.bn);
   const bool alone = t.waves * t.bm * t.bn * 4 > 80 * 1024;
   return 2.6 + (alone ? 1.0 : t.waves > 8 ? 0.5 : 0.0) + per_cu * (1.4e-5 * kib + 1.2e-4 * t.bm * t.bn);
@@ -466,8 +467,9 @@ w8a8_status run_gemm(const Plan& pl, int dt, int epi, const void* A, int64_t lda
 // reduces them itself.
 w8a8_status run_gemm_raw(const Plan& pl, int dt, const void* A, int64_t lda, int64_t m,
                          const void* B, int64_t n, int64_t k, void* part, hipStream_t st,
-                         QLoad ql = QLoad()) {
+                         QLoad ql = QLoad(), bool a_packed = false) {
   GemmParams p{};
+  p.a_packed = a_packed ? 1 : 0;
   p.a_x = ql.x;
   p.a_delta = ql.delta;
   p.a_ld = k;
@@ -590,16 +592,27 @@ bool bf16_h_packed(int64_t m, int64_t d, int64_t f) {
          packs(plan_gemm(m, d, f, DT_BF16, false, false));
 }
 
+// A block's row-major input is worth a launch that packs it where its rows are
+// long and, below 2048 columns, not so many that the products outlast the fetch
+// (d x f, rows / packed: 1152 x 6912 at M = 128 24.1 / 24.1 us, 256 40.0 / 35.4, 512
+// 46.6 / 44.8, 1021 60.3 / 63.1, 2048 99.2 / 100.6; 1536 x 4608 at M = 200 39.7 / 29.1,
+// 777 55.1 / 51.9; 640 x 2048 at M = 256 13.6 / 14.5; 2560 x 10240 at M = 128
+// 67.4 / 49.7, 1021 175 / 162, 2048 306 / 293).  In the stack the glue packs it.
+bool bf16_x_packed(int64_t m, int64_t d, int64_t f) {
+  return m >= 128 && (d >= 2048 || (d >= 1024 && m < 1000)) && d % kFragK16 == 0 &&
+         packs(plan_gemm(m, f, d, DT_BF16, true, false));
+}
+
 struct Bf16FfnWs {
-  size_t h, gemm_gu, gemm_dn, total;
+  size_t h, gemm_dn, x, total;
 };
-Bf16FfnWs bf16_ffn_ws(int64_t m, int64_t d, int64_t f, bool packed) {
+Bf16FfnWs bf16_ffn_ws(int64_t m, int64_t d, int64_t f, bool packed, bool x_packed = false) {
   Bf16FfnWs w;
   Plan pd = plan_gemm(m, d, f, DT_BF16, false, !packed);
   w.h = 0;
   w.gemm_dn = align256(packed ? w8a8_packed_bf16_bytes(m, f) : (size_t)m * f * 2);
-  w.total = w.gemm_dn + plan_ws_bytes(pd, m, d);
-  w.gemm_gu = 0;
+  w.x = w.gemm_dn + plan_ws_bytes(pd, m, d);
+  w.total = w.x + (x_packed ? align256(w8a8_packed_bf16_bytes(m, d)) : 0);
   return w;
 }
 
@@ -610,8 +623,9 @@ size_t bf16_linear_ws(int64_t m, int64_t n, int64_t k) {
 // Stack workspace: token stream, next-consumer input (bf16 and codes), FFN
 // intermediates, the down projection's raw partial sums, the lm_head's GEMM
 // workspace.
-// INT8 down projection inside the stack: its split-K sums are reduced by the
-// glue launch, so the plan may split K more freely than a standalone call.
+// INT8 down projection inside the stack: the glue adds partial sums of a K split,
+// so K may be split over workgroups more freely than in a standalone call (int32
+// sums are exact: the same bits; bf16 layers keep the standalone block's plan).
 // Planner overrides: DOWN_TILE, DOWN_SPLITS.
 Plan stack_down_plan(int64_t m, int64_t d, int64_t f) {
   Plan p = plan_gemm(m, d, f, DT_I8, false);
@@ -634,14 +648,40 @@ Plan stack_down_plan(int64_t m, int64_t d, int64_t f) {
     }
     return p;
   }
-  // DOWN_TILE / DOWN_SPLITS: experiments with split tiles, whose partial sums
-  // the glue adds (the planner itself takes whole sums on K-wave or ring tiles)
-  p.tile = plan_override("DOWN_TILE", p.tile);
-  if (tile_is_kwave(p.tile) || tile_is_ring(p.tile)) return p;
   const int64_t kb = ceil_div(f, kFragK8);
+  // A K-wave tile of a few splits where whole sums leave CUs idle or make small
+  // tiles re-read their operands: larger tiles, each over a part of K, for one
+  // more pass over m x d partial sums a split.  The line is the cost model's; over
+  // every tile and 1 ... 4 splits at M = 64 ... 1024 it picks the fastest (stack of
+  // 26 int8 layers and the lm_head, 1152 x 6912: M = 64 766 -> 719 us, 128
+  // 866 -> 805, 256 1052 -> 975, 512 1366 -> 1285, 1024 1908 -> 1862; M = 777 stays whole,
+  // 1702 against 1768).
+  const bool forced = plan_override("GEMM_TILE", -1) >= 0 || plan_override("DOWN_TILE", -1) >= 0 ||
+                      plan_override("DOWN_SPLITS", -1) >= 0;
+  if (m > 1 && !forced && (tile_is_kwave(p.tile) || tile_is_ring(p.tile))) {
+    double us = 0;
+    plan_kwave_or_ring(m, d, f, DT_I8, false, false, &us);
+    for (const KwTile& t : kKwTiles)
+      for (int s = 2; s <= 4; ++s) {
+        const int64_t chunk = ceil_div(kb, s);
+        if (chunk < 8 || ceil_div(kb, chunk) != s) continue;
+        const double v = kwave_us(t, m, d, f, false, false, s) + 0.5 +
+                         1.2e-6 * s * (double)m * (double)d;
+        if (v < us) {
+          us = v;
+          p.tile = t.tile;
+          p.splits = s;
+          p.kchunk = (int)chunk;
+        }
+      }
+    return p;
+  }
+  p.tile = plan_override("DOWN_TILE", p.tile);
+  if (tile_is_ring(p.tile)) return p;
   const int splits = std::max(1, plan_override("DOWN_SPLITS", p.splits));
   p.kchunk = (int)ceil_div(kb, splits);
   p.splits = (int)ceil_div(kb, p.kchunk);
+  if (tile_is_kwave(p.tile)) return p;
   plan_order(p, m, d);
   if (plan_override("NT_OUT", -1) < 0)
     p.nt_out = plan_override("NT_DOWN", (int64_t)p.splits * m * d * 4 >= (2 << 20) ? 1 : 0) != 0;
@@ -653,8 +693,8 @@ struct StackWs {
 };
 StackWs stack_ws(int64_t m, int64_t d, int64_t f, int64_t vocab) {
   StackWs w;
-  const Plan p8 = stack_down_plan(m, d, f), p16 = plan_gemm(m, d, f, DT_BF16, false);
-  // (a packed bf16 operand's plan is a K-wave or ring tile: one split)
+  const Plan p8 = stack_down_plan(m, d, f);
+  const Plan p16 = plan_gemm(m, d, f, DT_BF16, false, !bf16_h_packed(m, d, f));
   // at one token the persistent decode kernel may write up to kGlueMaxSplits planes
   const int planes = std::max({p8.splits, p16.splits, m == 1 ? kGlueMaxSplits : 1});
   const size_t part = (size_t)planes * m * d * 4;
@@ -739,14 +779,20 @@ w8a8_status bf16_linear_impl(const void* x, int64_t m, const void* wp, int64_t n
 
 w8a8_status bf16_ffn_impl(const w8a8_bf16_ffn_desc* d, const void* x, int64_t m, void* y,
                           void* ws, size_t ws_bytes, hipStream_t st) {
-  // whole fragments of h need up to 15 more rows than its m: a workspace of the
-  // plain size keeps h in rows
+  // whole fragments of h need up to 15 more rows than its m, a packed x room of
+  // its own: a smaller workspace keeps the one and the other in rows
   const bool packed = bf16_h_packed(m, d->d, d->f) && ws_bytes >= bf16_ffn_ws(m, d->d, d->f, true).total;
-  Bf16FfnWs w = bf16_ffn_ws(m, d->d, d->f, packed);
+  const bool xp = packed && bf16_x_packed(m, d->d, d->f) &&
+                  ws_bytes >= bf16_ffn_ws(m, d->d, d->f, true, true).total;
+  Bf16FfnWs w = bf16_ffn_ws(m, d->d, d->f, packed, xp);
   char* base = (char*)ws;
-  Plan pg = plan_gemm(m, d->f, d->d, DT_BF16, true);
+  if (xp) {
+    CHECK(hip_check(launch_pack_bf16(x, m, d->d, base + w.x, st), "pack_bf16"));
+    x = base + w.x;
+  }
+  Plan pg = plan_gemm(m, d->f, d->d, DT_BF16, true, !xp);
   CHECK(run_gemm(pg, DT_BF16, EPI_GLU, x, d->d, m, d->wp_gate, d->wp_up, d->f, d->d, nullptr, nullptr,
-                 nullptr, base + w.h, d->f, nullptr, st, QLoad(), false, packed));
+                 nullptr, base + w.h, d->f, nullptr, st, QLoad(), xp, packed));
   Plan pd = plan_gemm(m, d->d, d->f, DT_BF16, false, !packed);
   return run_gemm(pd, DT_BF16, EPI_BF16, base + w.h, d->f, m, d->wp_down, nullptr, d->d, d->f,
                   nullptr, nullptr, nullptr, y, d->d, base + w.gemm_dn, st, QLoad(), packed);
@@ -781,7 +827,8 @@ size_t w8a8_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
 size_t w8a8_bf16_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
   if (m < 1 || d < 1 || f < 1) return 0;
   const size_t rows = bf16_ffn_ws(m, d, f, false).total;
-  return bf16_h_packed(m, d, f) ? std::max(rows, bf16_ffn_ws(m, d, f, true).total) : rows;
+  if (!bf16_h_packed(m, d, f)) return rows;
+  return std::max(rows, bf16_ffn_ws(m, d, f, true, bf16_x_packed(m, d, f)).total);
 }
 
 size_t w8a8_bf16_linear_workspace_bytes(int64_t m, int64_t n, int64_t k) {
@@ -1382,15 +1429,20 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
   int8_t* qh = (int8_t*)(base + w.qh);
   float* sh = (float*)(base + w.sh);
   void* part = base + w.part;
-  // bf16 layers: the block input a and h in the packed layout (beyond m rows
-  // they reach into the code regions behind them, q and qh, which a bf16 layer
-  // does not use and which from 32 rows on are larger than the 15 rows)
-  const bool packed = bf16_h_packed(m, d, f) && d % kFragK16 == 0 &&
-                      packs(plan_gemm(m, f, d, DT_BF16, true, false));
-  const Plan p8 = stack_down_plan(m, d, f), p16 = plan_gemm(m, d, f, DT_BF16, false, !packed);
-  const Plan pg8 = plan_gemm(m, f, d, DT_I8, true), pg16 = plan_gemm(m, f, d, DT_BF16, true, !packed);
-  // every call starts with a clear failure word (w8a8_ffn_stack_status)
-  CHECK(hip_check(launch_dec_status_clear((DecCtl*)(base + w.ctl), st), "status clear"));
+  // bf16 layers: h, and the block input a, in the packed layout where the
+  // standalone block packs them, so both give the same bits.  Beyond m rows they
+  // reach into the code regions behind them, q and qh, which a bf16 layer does not
+  // use and which from 32 rows on are larger than the 15 rows.
+  const bool h_packed = bf16_h_packed(m, d, f), a_packed = h_packed && bf16_x_packed(m, d, f);
+  const Plan p8 = stack_down_plan(m, d, f);
+  const Plan p16 = plan_gemm(m, d, f, DT_BF16, false, !h_packed);
+  const Plan pg8 = plan_gemm(m, f, d, DT_I8, true), pg16 = plan_gemm(m, f, d, DT_BF16, true, !a_packed);
+  // every call starts with a clear failure word (w8a8_ffn_stack_status): at one
+  // token a launch clears it and the first decode run's counters, above the
+  // first glue clears it
+  DecCtl* ctl = (DecCtl*)(base + w.ctl);
+  bool ctl_cleared = m == 1;
+  if (ctl_cleared) CHECK(hip_check(launch_dec_clear(ctl, st), "clear"));
 
   // At one token, runs of consecutive INT8 layers go to the persistent decode
   // kernel (one launch per run of up to kDecMaxLayers layers) when the device
@@ -1422,6 +1474,7 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
     g.kp = round_up(d, 64);
     g.x_in = xin;
     g.x_out = xbuf[nxt];
+    if (m > 1 && l == 0) g.clear = ctl->fail;
     if (hidden && l > 0) g.x_copy = hidden + (l - 1) * m * d;
     if (l > 0) {
       const bool i8 = prec[l - 1] != 0;
@@ -1444,7 +1497,7 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
       g.delta = l < desc->n_layers ? desc->int8_ffn[l].delta_gu : desc->lm_head_int8.delta;
     } else {
       g.a = a;
-      g.a_packed = packed && l < desc->n_layers;  // the lm_head reads rows
+      g.a_packed = a_packed && l < desc->n_layers;  // the lm_head reads rows
     }
     CHECK(hip_check(launch_glue(g, st), "glue"));
     xin = xbuf[nxt];
@@ -1495,9 +1548,10 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
       P.scratch = base + w.dec;
       P.layout = decode_layout(d, f, dec_splits);
       P.splits = dec_splits;
-      P.ctl = (DecCtl*)(base + w.ctl);
+      P.ctl = ctl;
       P.spin_limit = plan_override("DEC_SPIN_LIMIT", P.spin_limit);  // failure-path tests
-      CHECK(hip_check(launch_decode_ffn(P, dec_grid, st), "decode_ffn"));
+      CHECK(hip_check(launch_decode_ffn(P, dec_grid, ctl_cleared, st), "decode_ffn"));
+      ctl_cleared = false;
       xin = xbuf[nxt];  // the token stream after layer l1 - 2
       nxt ^= 1;
       for (int64_t j = l; j < l1; ++j) out_splits[j] = dec_splits;
@@ -1548,12 +1602,12 @@ w8a8_status stack_run(const w8a8_stack_desc* desc, const uint8_t* prec, int lm_h
     } else {
       const w8a8_bf16_ffn_desc* L = &desc->bf16_ffn[l];
       CHECK(run_gemm(pg16, DT_BF16, EPI_GLU, a, d, m, L->wp_gate, L->wp_up, f, d, nullptr, nullptr,
-                     nullptr, h, f, nullptr, st, QLoad(), packed, packed));
+                     nullptr, h, f, nullptr, st, QLoad(), a_packed, h_packed));
       if (whole(l))
         CHECK(run_gemm(p16, DT_BF16, EPI_BF16, h, f, m, L->wp_down, nullptr, d, f, nullptr, nullptr,
-                       nullptr, part, d, nullptr, st, QLoad(), packed));
+                       nullptr, part, d, nullptr, st, QLoad(), h_packed));
       else
-        CHECK(run_gemm_raw(p16, DT_BF16, h, f, m, L->wp_down, d, f, part, st));
+        CHECK(run_gemm_raw(p16, DT_BF16, h, f, m, L->wp_down, d, f, part, st, QLoad(), h_packed));
     }
   }
   const int64_t V = desc->vocab, nl = desc->n_layers;

@@ -55,16 +55,13 @@ namespace {
 constexpr int kDecNW = 8;  // waves per workgroup
 constexpr int kDecThreads = 64 * kDecNW;
 
-__global__ void dec_clear_kernel(DecCtl* ctl) {
+__global__ void dec_clear_kernel(DecCtl* ctl, int status) {
   if (threadIdx.x < kDecGroups) ctl->grp[threadIdx.x][0] = 0u;
   if (threadIdx.x == 0) {
     ctl->top[0] = 0u;
     ctl->err[0] = 0u;
+    if (status) ctl->fail[0] = 0u;
   }
-}
-
-__global__ void dec_status_clear_kernel(DecCtl* ctl) {
-  if (threadIdx.x == 0) ctl->fail[0] = 0u;
 }
 
 // Arrival at barrier k (1, 2, ...): every wave waits until its own stores are
@@ -454,7 +451,7 @@ DecLayout decode_layout(int64_t d, int64_t f, int splits) {
   return L;
 }
 
-hipError_t launch_decode_ffn(const DecParams& P, int grid, hipStream_t st) {
+hipError_t launch_decode_ffn(const DecParams& P, int grid, bool cleared, hipStream_t st) {
   const DecLayout want = decode_layout(P.d, P.f, P.splits);
   if (P.n_layers < 1 || P.n_layers > kDecMaxLayers || grid < 1 || !P.ctl || !P.scratch ||
       !P.part || !P.sh || !P.x_out || !P.x_in || P.splits != decode_splits(P.d, P.f, grid) ||
@@ -466,15 +463,17 @@ hipError_t launch_decode_ffn(const DecParams& P, int grid, hipStream_t st) {
     const DecLayer& L = P.L[j];
     if (!L.wg || !L.wu || !L.sg || !L.su || !L.wd || !L.sd) return hipErrorInvalidValue;
   }
-  dec_clear_kernel<<<1, 64, 0, st>>>(P.ctl);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!cleared) {
+    dec_clear_kernel<<<1, 64, 0, st>>>(P.ctl, 0);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   decode_ffn_kernel<<<grid, kDecThreads, 0, st>>>(P);
   return hipGetLastError();
 }
 
-hipError_t launch_dec_status_clear(DecCtl* ctl, hipStream_t st) {
-  dec_status_clear_kernel<<<1, 64, 0, st>>>(ctl);
+hipError_t launch_dec_clear(DecCtl* ctl, hipStream_t st) {
+  dec_clear_kernel<<<1, 64, 0, st>>>(ctl, 1);
   return hipGetLastError();
 }
 

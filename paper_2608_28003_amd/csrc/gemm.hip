@@ -883,7 +883,7 @@ int device_cus() {
 hipError_t launch_gemm_tile(int dt, int epi, int tile, const GemmParams& p, hipStream_t st) {
   if (!gemm_params_ok(dt, epi, p, 0)) return hipErrorInvalidValue;
   if (tile_is_kwave(tile))
-    return p.splits == 1 ? launch_gemm_kwave(dt, epi, tile, p, st) : hipErrorInvalidValue;
+    return launch_gemm_kwave(dt, epi, tile, p, st);
   if (tile_is_ring(tile))
     return p.splits == 1 ? launch_gemm_ring(dt, epi, tile, p, device_cus(), st) : hipErrorInvalidValue;
   switch (dt) {

@@ -7,7 +7,8 @@
 // meet once, in LDS, after the K loop.  No operand passes through LDS and no
 // barrier stands in the K loop, so the waves' loads and matrix instructions
 // overlap freely, and a long K needs no split over workgroups: no partial sums
-// in memory and no reduction launch.
+// in memory and no reduction launch.  (Where the consumer adds partial sums by
+// itself, raw sums can be split over workgroups all the same.)
 //
 // What bounds it: the register-return path of a CU (64 B a cycle), at
 // (TM + TN) KiB per fragment column against 16 TM TN / 4 matrix cycles, so the
@@ -35,9 +36,12 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void gemm_kwave_kernel(GemmParams 
   const int n_tiles = (p.rb_b + TH - 1) / TH;
   // XCD blockIdx % 8 takes a contiguous range of tiles; the walk goes through
   // bands of group_m tile rows, so a range is a compact block of both operands
-  const int total = m_tiles * n_tiles, per_xcd = (total + 7) / 8;
-  const int tile = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
-  if (tile >= total) return;  // whole workgroup, before any barrier
+  // (with K splits the ranges of every tile's first split come first, and so on)
+  const int tiles = m_tiles * n_tiles, total = tiles * p.splits, per_xcd = (total + 7) / 8;
+  const int item = (int)(blockIdx.x % 8) * per_xcd + (int)(blockIdx.x / 8);
+  if (item >= total) return;  // whole workgroup, before any barrier
+  const int z = item / tiles, tile = item % tiles;
+  const int kb0 = z * p.kchunk, kbs = min(p.kchunk, p.kb_count - kb0);  // this split's columns
   const int band_tiles = p.group_m * n_tiles, band = tile / band_tiles, in_band = tile % band_tiles;
   const int gm = min(p.group_m, m_tiles - band * p.group_m);
   const int mt = band * p.group_m + in_band % gm, nt = in_band / gm;
@@ -50,26 +54,26 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void gemm_kwave_kernel(GemmParams 
   for (int i = 0; i < TM; ++i) {
     if (BF16 && !p.a_packed) {  // row-major: lane l reads row l % 16, columns (l / 16) * 8 .. + 7
       pa[i] = reinterpret_cast<const int8_t*>(reinterpret_cast<const uint16_t*>(p.A) +
-                                              (int64_t)mt * TM * 16 * p.lda);
+                                              (int64_t)mt * TM * 16 * p.lda + kb0 * kFragK16);
       const int r = min((mt * TM + i) * 16 + (lane & 15), p.M - 1) - mt * TM * 16;
       arow[BF16 ? i : 0] = (unsigned)r * (unsigned)(p.lda * 2) + (lane >> 4) * 16;
     } else {
       arow[BF16 ? i : 0] = lane * 16;
       pa[i] = reinterpret_cast<const int8_t*>(p.A) +
-              frag_offset(min(mt * TM + i, p.rb_a - 1), 0, p.kb_count);
+              frag_offset(min(mt * TM + i, p.rb_a - 1), kb0, p.kb_count);
     }
   }
 #pragma unroll
   for (int t = 0; t < TN; ++t) {
     const void* base = GLU && t >= TH ? p.B2 : p.B;
     pb[t] = reinterpret_cast<const int8_t*>(base) +
-            frag_offset(min(nt * TH + (GLU && t >= TH ? t - TH : t), p.rb_b - 1), 0, p.kb_count);
+            frag_offset(min(nt * TH + (GLU && t >= TH ? t - TH : t), p.rb_b - 1), kb0, p.kb_count);
   }
 
   const unsigned a_step = BF16 && !p.a_packed ? kFragK16 * 2 : kFragBytes;
 
   // this wave's steps: fragment columns KP (wave + NW j) .. + KP - 1
-  const int all = (p.kb_count + KP - 1) / KP;
+  const int all = (kbs + KP - 1) / KP;
   const int n = all > wave ? (all - wave + NW - 1) / NW : 0;
   AccT acc[TM][TN];
 #pragma unroll
@@ -86,13 +90,13 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void gemm_kwave_kernel(GemmParams 
   auto load = [&](Frags& f) {
 #pragma unroll
     for (int k = 0; k < KP; ++k) {
-      const unsigned off = (unsigned)(min(col, p.kb_count - KP) + k) * kFragBytes + lane * 16;
+      const unsigned off = (unsigned)(min(col, kbs - KP) + k) * kFragBytes + lane * 16;
 #pragma unroll
       for (int t = 0; t < TN; ++t) f.b[k][t] = *reinterpret_cast<const v4i*>(pb[t] + off);
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
         const unsigned aoff =
-            BF16 ? arow[BF16 ? i : 0] + (unsigned)min(col, p.kb_count - 1) * a_step : off;
+            BF16 ? arow[BF16 ? i : 0] + (unsigned)min(col, kbs - 1) * a_step : off;
         f.a[k][i] = *reinterpret_cast<const v4i*>(pa[i] + aoff);
       }
     }
@@ -202,7 +206,8 @@ __global__ __launch_bounds__(64 * NW, NW / 4) void gemm_kwave_kernel(GemmParams 
         }
       }
     }
-    char* dst = reinterpret_cast<char*>(p.out) + ((int64_t)row * p.ldo + c0) * ESZ;
+    char* dst = reinterpret_cast<char*>(p.out) +
+                (((int64_t)z * p.M + row) * p.ldo + c0) * ESZ;  // partial sums: one plane a split
     if (BF16 && ESZ == 2 && p.out_packed)  // packed bf16 layout (the next GEMM's A operand)
       dst = reinterpret_cast<char*>(p.out) + frag_offset(row >> 4, c0 / kFragK16, p.ldo / kFragK16) +
             ((row & 15) + 16 * ((c0 % kFragK16) / 8)) * 16;
@@ -241,7 +246,12 @@ hipError_t launch_kwave(const GemmParams& p, hipStream_t st) {
     attr_set = true;
   }
   constexpr int TH = EPI == EPI_GLU ? TN / 2 : TN;
-  const int64_t tiles = (int64_t)((p.M + 16 * TM - 1) / (16 * TM)) * ((p.rb_b + TH - 1) / TH);
+  // partial sums are raw
+  if (p.splits > 1 && ((EPI != EPI_I32 && !(DT == DT_BF16 && EPI == EPI_F32)) || !p.out ||
+                       p.kchunk % frags_per_mma<DT>()))
+    return hipErrorInvalidValue;
+  const int64_t tiles =
+      (int64_t)((p.M + 16 * TM - 1) / (16 * TM)) * ((p.rb_b + TH - 1) / TH) * p.splits;
   const int lds = tiles <= device_cus() && sums < spread ? spread : sums;
   GemmParams q = p;
   if (q.group_m < 1) q.group_m = 8;

@@ -86,7 +86,8 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(const uint16_t* x,
 // MAXZ: split-K partial sums held in registers (more splits stream from
 // memory); 4 for the stack's plans keeps the kernel at ~80 registers, so
 // every row of a 2048-token batch is resident at once.
-template <int NT, int MAXZ>
+// Y: the FFN output is bf16 (g.y), not partial sums.
+template <int NT, int MAXZ, bool Y>
 __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
   __shared__ float red_y[16], red_x[16], red_q[16];
   const int64_t r = blockIdx.x;
@@ -94,6 +95,7 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
   const int64_t d = g.d;
   const int64_t chunks = d / 8;
   const int64_t kb_count = g.kp / kFragK8;
+  if (g.clear && r == 0 && t == 0) *g.clear = 0u;
   auto store_codes8 = [&](int64_t c, uint2 v) {  // 8 codes of columns [8c, 8c + 8)
     const int64_t col = c * 8;
     const int64_t off = frag_offset(r >> 4, col / kFragK8, kb_count) +
@@ -122,7 +124,7 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       d0 = *reinterpret_cast<const float4*>(g.delta + col0);
       d1 = *reinterpret_cast<const float4*>(g.delta + col0 + 4);
     }
-    if (g.y) {
+    if constexpr (Y) {
       yraw = *reinterpret_cast<const uint4*>(g.y + r * d + col0);
     } else if (g.part) {
       const int32_t* pp = reinterpret_cast<const int32_t*>(g.part) + r * d + col0;
@@ -145,11 +147,11 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       xv[2 * j + 1] = bf16_bits_to_float(w[j] >> 16);
     }
   }
-  if (g.part || g.y) {
+  if (Y || g.part) {
     float y[8];
     float ss = 0.0f;
     if (own) {
-      if (g.y) {
+      if constexpr (Y) {
         const uint32_t w[4] = {yraw.x, yraw.y, yraw.z, yraw.w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(NT) void glue_kernel(GlueParams g) {
       }
     }
   }
-  const bool write_out = g.x_out && (g.part || g.y || g.x_out != g.x_in);
+  const bool write_out = g.x_out && (Y || g.part || g.x_out != g.x_in);
   if (own && (write_out || g.x_copy)) {
     uint4 o;
     o.x = (uint32_t)float_to_bf16_bits(xv[0]) | ((uint32_t)float_to_bf16_bits(xv[1]) << 16);
@@ -282,16 +284,21 @@ hipError_t launch_glue(const GlueParams& g, hipStream_t st) {
   const int64_t per_row = std::max(g.d / 8, g.q ? g.kp / 8 : 0);
   const int64_t threads = std::min<int64_t>((per_row + 63) / 64 * 64, 1024);
   const bool few = !g.part || g.splits <= 4;
+  const dim3 grid((unsigned)rows), block((unsigned)threads);
   if (threads <= 256) {
-    if (few)
-      glue_kernel<256, 4><<<(unsigned)rows, (unsigned)threads, 0, st>>>(g);
+    if (g.y)
+      glue_kernel<256, 1, true><<<grid, block, 0, st>>>(g);
+    else if (few)
+      glue_kernel<256, 4, false><<<grid, block, 0, st>>>(g);
     else
-      glue_kernel<256, 8><<<(unsigned)rows, (unsigned)threads, 0, st>>>(g);
+      glue_kernel<256, 8, false><<<grid, block, 0, st>>>(g);
   } else {
-    if (few)
-      glue_kernel<1024, 4><<<(unsigned)rows, (unsigned)threads, 0, st>>>(g);
+    if (g.y)
+      glue_kernel<1024, 1, true><<<grid, block, 0, st>>>(g);
+    else if (few)
+      glue_kernel<1024, 4, false><<<grid, block, 0, st>>>(g);
     else
-      glue_kernel<1024, 8><<<(unsigned)rows, (unsigned)threads, 0, st>>>(g);
+      glue_kernel<1024, 8, false><<<grid, block, 0, st>>>(g);
   }
   return hipGetLastError();
 }

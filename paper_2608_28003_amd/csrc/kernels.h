@@ -189,6 +189,7 @@ struct GlueParams {
   int8_t* q = nullptr;                 // packed codes of the pre-norm output (optional)
   float* s = nullptr;                  // their per-row scales
   uint16_t* x_copy = nullptr;          // second copy of the token stream out (optional)
+  unsigned* clear = nullptr;           // a word to set to 0 (optional)
 };
 hipError_t launch_glue(const GlueParams& g, hipStream_t st);
 
@@ -204,8 +205,8 @@ struct DecCtl {                    // 256-byte lines
   unsigned grp[kDecGroups][64];    // arrivals per group (word 0)    } every launch
   unsigned err[64];                // word 0 nonzero: a wait of this launch gave up
   unsigned fail[64];               // word 0 nonzero: a wait gave up in some launch since
-                                   // the last launch_dec_status_clear (the run's outputs
-                                   // are NaN); read by w8a8_ffn_stack_status
+                                   // the stack call began (the run's outputs are NaN);
+                                   // read by w8a8_ffn_stack_status
 };
 struct DecLayer {
   const void* wg;      // packed gate weights (f x d)
@@ -259,9 +260,10 @@ int decode_grid(int device);
 // K splits of the down projection for this shape and grid, or 0 when the
 // shape does not fit the kernel.
 int decode_splits(int64_t d, int64_t f, int grid);
-hipError_t launch_decode_ffn(const DecParams& P, int grid, hipStream_t st);
-// Clears ctl->fail (start of every stack call).
-hipError_t launch_dec_status_clear(DecCtl* ctl, hipStream_t st);
+// cleared: launch_dec_clear ran on the counters since the last launch.
+hipError_t launch_decode_ffn(const DecParams& P, int grid, bool cleared, hipStream_t st);
+// Clears all of ctl (start of a one-token stack call).
+hipError_t launch_dec_clear(DecCtl* ctl, hipStream_t st);
 
 // SQNR of test against ref over n elements (bf16 or f32): part holds
 // 2 * sqnr_groups(n) doubles of scratch, out receives {sum ref^2,

@@ -143,3 +143,35 @@ def test_bf16_block_packed_activations(m, d, f):
     ref = h @ torch.from_numpy(cfg["w_down"].astype(np.uint32) << 16).to(torch.int32).view(torch.float32).to(DEV).double().t()
     for name, got in (("packed", y), ("rows", y_rows)):
         assert float((got - ref).norm() / ref.norm()) <= 2.0 ** -8, name
+
+
+@pytest.mark.parametrize("m", [33, 100, 300])
+def test_stack_down_splits(m):
+    """K-wave tiles over parts of K, added by the glue: int8 sums are exact, so the
+    stack's logits have the same bits for every tile and split (ragged last splits
+    among them)."""
+    d, f, v = 208 * 4, 2112, 512
+    g = torch.Generator().manual_seed(m)
+    rnd = lambda *s: (torch.randn(s, generator=g) * 0.05).bfloat16().to(DEV)
+    ws = [(rnd(f, d), rnd(f, d), rnd(d, f)) for _ in range(2)]
+    one = lambda n: torch.ones(n, device=DEV)
+    head = w8a8.LinearW8A8.from_weight(rnd(v, d), one(d))
+    stack = w8a8.Stack([w8a8.FfnW8A8.from_weights(*w, one(d), one(f)) for w in ws],
+                       [w8a8.FfnBF16.from_weights(*w) for w in ws], head, None, v)
+    x = torch.randn(m, d, generator=g).bfloat16().to(DEV)
+
+    def run(prec):
+        buf = torch.full((w8a8.stack_workspace_bytes(m, d, f, v),), 255, dtype=torch.uint8, device=DEV)
+        return stack.run(x, np.array(prec, np.uint8), True, ws=buf).double()
+
+    w8a8.set_plan_override("DOWN_TILE", 34)
+    w8a8.set_plan_override("DOWN_SPLITS", 1)
+    ref = run([1, 1])
+    for tile in (None,) + KWAVE:
+        for splits in (2, 3, 4):
+            print("down splits", m, tile, splits, flush=True)
+            w8a8.clear_plan_overrides()
+            if tile is not None:
+                w8a8.set_plan_override("DOWN_TILE", tile)
+                w8a8.set_plan_override("DOWN_SPLITS", splits)
+            assert torch.equal(run([1, 1]), ref), (tile, splits)
