@@ -49,6 +49,36 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   return (uint32_t)float_to_bf16_bits(lo) | ((uint32_t)float_to_bf16_bits(hi) << 16);
 }
 
+// Sets of scales in LDS.  At a tile's epilogue the producer stands S steps ahead
+// and has fetched the next tile's scales as well: with nk steps a tile the live
+// tiles are S / nk + 2, so S + 2 sets serve the shortest K.
+constexpr int ring_scale_sets(int S) { return S + 2; }
+
+// The order of producer and consumer, replayed: whether every tile's set still
+// holds its own scales at the tile's epilogue (only nk <= S needs more than two).
+constexpr bool ring_scales_live(int S, int sets) {
+  for (int nk = 1; nk <= S + 1; ++nk) {
+    const int tiles = 3 * S + 6;
+    int owner[16] = {}, pq = 0, pj = 0;
+    auto advance = [&]() {  // after an issue, as in ring_body
+      if (++pj < nk) return;
+      if (pq + 1 < tiles) {
+        ++pq;
+        pj = 0;
+        owner[pq % sets] = pq;
+      } else {
+        --pj;
+      }
+    };
+    for (int j = 0; j < S; ++j) advance();
+    for (int q = 0; q < tiles; ++q) {
+      for (int j = 0; j < nk; ++j) advance();
+      if (owner[q % sets] != q) return false;
+    }
+  }
+  return true;
+}
+
 template <int DT, int EPI, int TM, int TNA, int TNB, int S, int KS>
 struct Ring {
   static constexpr bool GLU = EPI == EPI_GLU, BF16 = DT == DT_BF16;
@@ -58,7 +88,9 @@ struct Ring {
   static constexpr int PIECES = NF * KS, PF = (PIECES + kRingWaves - 1) / kRingWaves;
   static constexpr int NC = (BNH + 63) / 64;                    // 64-wide pieces of the column scales
   static constexpr int NSC = SCALED ? TM + NC * (GLU ? 2 : 1) : 0;
-  static constexpr int LDS = S * PIECES * kFragBytes + 2 * NSC * 256;
+  static constexpr int SETS = ring_scale_sets(S);
+  static constexpr int LDS = S * PIECES * kFragBytes + SETS * NSC * 256;
+  static_assert(ring_scales_live(S, SETS), "a tile's scales must live until its epilogue");
   static_assert(NSC <= kRingWaves, "one scale piece per wave");
   static_assert(KS % frags_per_mma<DT>() == 0, "a stage must hold whole MFMA K steps");
   static_assert(LDS <= 160 * 1024, "LDS");
@@ -75,7 +107,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
   constexpr int PF = R::PF, NF = R::NF, NB = R::NB;
   const int wm = wave & 3;
   const int c0 = wave < 4 ? 0 : (GLU ? TNA / 2 : TNA);  // this wave's first column block
-  float* sc = reinterpret_cast<float*>(lds + S * R::PIECES * 64);  // two sets of scales
+  float* sc = reinterpret_cast<float*>(lds + S * R::PIECES * 64);  // R::SETS sets of scales
 
   // tiles: XCD blockIdx % 8 takes a contiguous range of a walk through bands of
   // group_m tile rows (M fastest), its workgroups take them in turn
@@ -97,7 +129,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
   const int rot = p.rotate ? (int)((blockIdx.x * 5u) % (unsigned)nk) : 0;
   const int8_t* src[PF];
   unsigned voff[BF16 ? PF : 1], step_bytes[BF16 ? PF : 1];
-  int pq = 0, pj = 0, pslot = 0;
+  int pq = 0, pj = 0, pslot = 0, pset = 0;
   auto producer_item = [&]() {
     int mt, nt;
     item(pq, mt, nt);
@@ -145,7 +177,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
         const int c = (piece - TM - (up ? R::NC : 0)) * 64 + lane;
         g = (up ? p.s_b2 : p.s_b) + min(nt * R::BNH + c, p.N - 1);
       }
-      ring_dma4(g, sc + (pq & 1) * R::NSC * 64 + piece * 64);
+      ring_dma4(g, sc + pset * R::NSC * 64 + piece * 64);
     }
   };
   auto issue = [&]() {
@@ -165,6 +197,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
       if (pq + 1 < n_items) {
         ++pq;
         pj = 0;
+        pset = pset + 1 == R::SETS ? 0 : pset + 1;
         producer_item();
       } else {
         --pj;  // past the last tile: its last stage again, never read
@@ -247,7 +280,8 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
   };
 
   const bool vec = (p.ldo & (EPI == EPI_I32 || EPI == EPI_F32 ? 3 : 7)) == 0;
-  for (int q = 0; q < n_items; ++q) {
+  int cset = 0;
+  for (int q = 0; q < n_items; ++q, cset = cset + 1 == R::SETS ? 0 : cset + 1) {
     int mt, nt;
     item(q, mt, nt);
 #pragma unroll
@@ -269,7 +303,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
     const int rloc = wm * TM * 16 + (lane & 15);
     const int row0 = mt * R::BM + rloc, col0 = nt * R::BNH + c0 * 16;
     const bool full = vec && mt * R::BM + R::BM <= p.M && nt * R::BNH + R::BNH <= p.N;
-    const float* ss = sc + (q & 1) * R::NSC * 64;
+    const float* ss = sc + cset * R::NSC * 64;
     float4 sb[TH], sb2[GLU ? TH : 1];
     if constexpr (R::SCALED) {
 #pragma unroll
