@@ -295,6 +295,115 @@ int plan_kwave_or_ring(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a
   return best;
 }
 
+// ---- measured times of the plain products, in microseconds on 256 CUs
+//
+// The models above rank their own tiles well around the shapes that they were
+// fitted to, and know nothing of the LDS tiles.  These rows hold for K-wave, ring
+// and LDS tiles over K = 128 ... 14336, N = 256 ... 262144 and 33 ... 4096 rows
+// (21000 timings of one tile on one shape, weights cold; nine in ten of a row's
+// times lie within 10 % of it):
+//   c0 + rounds (e + s steps) + s2 steps ceil(tiles / (256 occ)) + w MB
+// with rounds = ceil(tiles / 256), steps the fragment columns of K and MB the
+// bytes of both operands and of a bf16 output.
+struct TileCost {
+  int tile, occ;  // occ: workgroups a CU holds at once
+  double c0, e, s, s2, w;
+};
+const TileCost kCostI8[] = {
+    {TILE_128x128, 2, 3.43, 2.82, 0.150, 0.262, 0.035},
+    {TILE_128x64, 2, 2.54, 1.67, 0.100, 0.226, 0.041},
+    {TILE_64x64_K2, 3, 1.99, 0.78, 0.000, 0.274, 0.096},
+    {TILE_256x128_W4, 2, 5.85, 4.23, 0.051, 0.595, 0.070},
+    {TILE_KW_64x144, 1, 1.40, 4.15, 0.148, 0.000, 0.103},
+    {TILE_KW_64x96, 1, 1.21, 2.75, 0.115, 0.000, 0.100},
+    {TILE_KW_64x64, 1, 2.44, 1.08, 0.088, 0.000, 0.091},
+    {TILE_KW_64x32_W8, 1, 2.04, 0.98, 0.057, 0.000, 0.120},
+    {TILE_KW_32x64, 1, 2.40, 0.53, 0.061, 0.000, 0.113},
+    {TILE_KW_32x32, 1, 2.28, 0.48, 0.036, 0.000, 0.123},
+    {TILE_KW_16x32, 1, 2.27, 0.64, 0.023, 0.000, 0.126},
+    {TILE_KW_16x16_W16, 1, 2.35, 1.02, 0.015, 0.000, 0.099},
+    {TILE_RING_256, 1, 0.17, 8.80, 0.524, 0.000, 0.087},
+    {TILE_RING_224, 1, 1.17, 6.72, 0.511, 0.000, 0.065},
+    {TILE_RING_192, 1, 2.08, 5.48, 0.492, 0.000, 0.060},
+    {TILE_RING_160, 1, 2.73, 4.10, 0.438, 0.000, 0.063},
+    {TILE_RING_128, 1, 3.13, 3.06, 0.393, 0.000, 0.070}};
+const TileCost kCostBf16[] = {
+    {TILE_128x128, 2, 4.57, 1.88, 0.287, 0.120, 0.023},
+    {TILE_128x64, 2, 3.46, 1.00, 0.226, 0.092, 0.051},
+    {TILE_64x64, 2, 3.53, 0.29, 0.082, 0.145, 0.056},
+    {TILE_256x128, 1, 1.15, 6.08, 0.568, 0.000, 0.019},
+    {TILE_KW_64x144, 1, 1.83, 3.69, 0.188, 0.000, 0.082},
+    {TILE_KW_64x96, 1, 1.86, 2.52, 0.156, 0.000, 0.072},
+    {TILE_KW_64x64, 1, 2.75, 1.29, 0.139, 0.000, 0.058},
+    {TILE_KW_64x32_W8, 1, 2.67, 1.17, 0.120, 0.000, 0.029},
+    {TILE_KW_32x64, 1, 2.75, 0.72, 0.081, 0.000, 0.070},
+    {TILE_KW_32x32, 1, 2.61, 0.80, 0.065, 0.000, 0.071},
+    {TILE_KW_16x32, 1, 2.99, 0.81, 0.041, 0.000, 0.052},
+    {TILE_KW_16x16_W16, 1, 3.59, 0.93, 0.034, 0.000, 0.059},
+    {TILE_RING_256, 1, 0.00, 8.57, 0.612, 0.000, 0.066},
+    {TILE_RING_224, 1, 1.86, 6.25, 0.625, 0.000, 0.041},
+    {TILE_RING_192, 1, 2.09, 5.57, 0.606, 0.000, 0.033},
+    {TILE_RING_160, 1, 3.63, 4.26, 0.614, 0.000, 0.000},
+    {TILE_RING_128, 1, 3.45, 3.11, 0.540, 0.000, 0.024}};
+const TileCost kCostF8[] = {
+    {TILE_64x64_K2, 3, 2.16, 0.71, 0.000, 0.265, 0.096},
+    {TILE_128x128_K2, 1, 1.13, 5.06, 0.338, 0.000, 0.081},
+    {TILE_KW_64x144, 1, 1.30, 4.31, 0.149, 0.000, 0.102},
+    {TILE_KW_64x96, 1, 1.24, 2.96, 0.111, 0.000, 0.101},
+    {TILE_KW_64x64, 1, 1.32, 2.29, 0.087, 0.000, 0.089},
+    {TILE_KW_64x32_W8, 1, 2.15, 0.99, 0.059, 0.000, 0.123},
+    {TILE_KW_32x64, 1, 2.10, 0.86, 0.057, 0.000, 0.100},
+    {TILE_KW_32x32, 1, 2.35, 0.57, 0.039, 0.000, 0.120},
+    {TILE_KW_16x32, 1, 2.09, 0.91, 0.023, 0.000, 0.126},
+    {TILE_KW_16x16_W16, 1, 2.62, 1.13, 0.016, 0.000, 0.100},
+    {TILE_RING_128, 1, 3.28, 2.48, 0.341, 0.000, 0.084}};
+
+double tile_us(const TileCost& t, int64_t m, int64_t n, int64_t k, int dt, int splits) {
+  const int64_t kb = ceil_div(k, dt == DT_BF16 ? kFragK16 : kFragK8);
+  const int64_t tiles = tiles_of(t.tile, m, n) * splits, steps = ceil_div(kb, splits);
+  const double out = (double)m * (double)n;
+  const double mb = ((double)(m + n) * (double)k * (dt == DT_BF16 ? 2 : 1) + 2 * out) * 1e-6;
+  return t.c0 + (double)ceil_div(tiles, 256) * (t.e + t.s * steps) +
+         t.s2 * steps * (double)ceil_div(tiles, 256 * t.occ) + t.w * mb +
+         (splits > 1 ? 2.7e-6 * splits * out : 0.0);  // partial sums, written and read
+}
+
+// `pick` (a K-wave or ring tile, or the lm_head's), or a tile whose measured
+// time is lower by more than the rows' error.  Candidates: the LDS tiles, for
+// very wide outputs (any = true) every tile, and for the long K of few bf16 columns
+// two LDS tiles with K in three parts.  What it takes back (a pass through the
+// linear): bf16 4096 x 640 x 14336 250 -> 129 us, 512 x 8192 x 6912 146 -> 110; FP8
+// 256 x 12288 x 128 14.2 -> 8.6; int8 256 x 16384 x 1152 24.5 -> 18.0.
+int plan_measured(int pick, int64_t m, int64_t n, int64_t k, int dt, bool any, int* splits) {
+  const TileCost* rows = dt == DT_I8 ? kCostI8 : dt == DT_BF16 ? kCostBf16 : kCostF8;
+  const int n_rows = (int)(dt == DT_I8     ? sizeof(kCostI8)
+                           : dt == DT_BF16 ? sizeof(kCostBf16)
+                                           : sizeof(kCostF8)) / (int)sizeof(TileCost);
+  const bool even = ceil_div(k, kFragK8) % 2 == 0;  // two fragment columns a stage
+  int best = -1;
+  double us = 0, us_pick = -1;
+  *splits = 1;
+  for (int i = 0; i < n_rows; ++i) {
+    const TileCost& t = rows[i];
+    if (t.tile == pick) us_pick = tile_us(t, m, n, k, dt, 1);
+    const bool lds = !tile_is_kwave(t.tile) && !tile_is_ring(t.tile);
+    if ((!any && !lds) || (!even && (t.tile == TILE_64x64_K2 || t.tile == TILE_128x128_K2))) continue;
+    const bool split = dt == DT_BF16 && k >= 4096 && n <= 4096 && tiles_of(t.tile, m, n) >= 64 &&
+                       (t.tile == TILE_256x128 || t.tile == TILE_128x128);
+    for (int sp = 1; sp <= (split ? 3 : 1); sp += 2) {
+      const double v = tile_us(t, m, n, k, dt, sp);
+      if (best < 0 || v < us) {
+        best = t.tile;
+        us = v;
+        *splits = sp;
+      }
+    }
+  }
+  if (best >= 0 && us_pick >= 0 && us < 0.93 * us_pick) return best;
+  *splits = 1;
+  return pick;
+}
+
 // Deterministic in (m, n, k, path); the workspace queries use the same plan.
 // Planner overrides: GEMM_TILE / GEMM_SPLITS (plain epilogues) and GLU_TILE
 // (gated epilogue).  a_rows: a bf16 A operand is row-major (not packed).
@@ -308,12 +417,15 @@ Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = 
   // (one launch less); up to 16 rows of very wide outputs (262144 columns:
   // M = 16 57.4 us against 62.0 on K-wave tiles, M = 32 73.8 against 67.6), of
   // long E4M3 reductions that fit its LDS (1152 x 6912, M = 8: 6.6 against
-  // 7.7 us), and up to 32 of row-major bf16 (the same, M = 8: 10.5 against 12.9).
+  // 7.7 us), and up to 32 of row-major bf16 (the same, M = 8: 10.5 against 12.9);
+  // up to 32 of very wide outputs with short rows, whose panel leaves room for
+  // several workgroups a CU (K = 640, M = 17: 262144 columns 38.9 against 43.0 us,
+  // FP8 38.1 against 47.6; 32000 columns 10.7 against 9.9).
   if (m <= 32 && !plan_override("NO_STREAM", 0) && plan_stream(p, m, n, kb, glu, f8)) {
     const bool fits = dt == DT_BF16 ? !glu && a_rows
                                     : m <= 16 && (wide || m * (k / 16) <= qload_capacity(p.nw) ||
                                                   (f8 && !glu && k >= 4096 && p.splits == 1));
-    if (fits || (wide && m <= 16)) {
+    if (fits || (wide && (m <= 16 || (k <= 640 && n >= 65536)))) {
       p.stream = true;
       return p;
     }
@@ -321,13 +433,15 @@ Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = 
   p = Plan();
   p.dt = dt;
   double us = 0;
+  int dflt_splits = 1;
   p.tile = plan_kwave_or_ring(m, n, k, dt, glu, a_rows, &us);
   if (wide) {
     // 262144 columns: 32 x 64 K-wave tiles to 32 rows; to 64 rows two-column
     // 64 x 64 tiles (int8 78.8 against 82.6 us on K-wave tiles; FP8 78.3 against
     // 83.6), to 128 rows 128 x 128 (int8 85.2 against 107 us on the ring, bf16
     // 160 against 167); above, the ring's widest tile (M = 256 113.9 against
-    // 128.9 us, M = 2048 661 against 822 us)
+    // 128.9 us, M = 2048 661 against 822 us).  Fewer columns may leave it fewer
+    // tiles than CUs, see plan_measured.
     if (m <= 32 && dt != DT_BF16)
       p.tile = TILE_KW_32x64;
     else if (m <= 64 && dt != DT_BF16 && kb % 2 == 0)
@@ -352,6 +466,11 @@ Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = 
       }
     }
   }
+  // (up to 32 int8 / E4M3 rows the choices above were measured themselves, as was
+  // the ring for very wide E4M3 outputs above 128: 129 x 16384 x 4096 31.8 us, LDS
+  // tiles 35.9; a packed bf16 A is read by the K-wave and the ring kernel only)
+  if (!glu && (dt == DT_BF16 ? a_rows : m > 32) && !(wide && f8 && m > 128))
+    p.tile = plan_measured(p.tile, m, n, k, dt, wide, &dflt_splits);
   const int want = glu ? plan_override("GLU_TILE", p.tile) : plan_override("GEMM_TILE", p.tile);
   // FP8 stages hold whole 128-deep MFMA steps: of the LDS tiles only the
   // two-column ones exist for it
@@ -360,7 +479,7 @@ Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = 
                                  want == TILE_GLU_256x64_K2_W8
                            : want == TILE_64x64_K2 || want == TILE_128x128_K2);
   if (exists) p.tile = want;
-  int64_t splits = plan_override("GEMM_SPLITS", 1);
+  int64_t splits = plan_override("GEMM_SPLITS", dflt_splits);
   if (glu || splits < 1 || tile_is_kwave(p.tile) || tile_is_ring(p.tile)) splits = 1;
   p.kchunk = (int)ceil_div(kb, splits);
   if (f8) p.kchunk = (int)round_up(p.kchunk, 2);
