@@ -53,7 +53,7 @@ __device__ __forceinline__ void load_bf16x4(const uint16_t* p, float (&v)[4]) {
   v[3] = bf16_bits_to_float(raw.y >> 16);
 }
 
-// Eight INT8 codes (exact in bf16) as a bf16 fragment.
+// INT8 code e of a word (exact in bf16)
 __device__ __forceinline__ float byte_f(uint32_t w, int e) {
   return (float)(int8_t)(uint8_t)(w >> (8 * e));
 }
@@ -254,11 +254,12 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
     }
     mx = fmaxf(mx, lane_xor<16>(mx));
     mx = fmaxf(mx, lane_xor<32>(mx));
-    const float corr = expf(run_m - mx);  // 0 on the first step
+    const float ref = mx == -INFINITY ? 0.0f : mx;  // scores of -inf only: weights of 0
+    const float corr = expf(run_m - ref);  // 0 on the first step
     float sum = 0.0f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      sc[i] = expf(sc[i] - mx);  // 0 for rows past the end
+      sc[i] = expf(sc[i] - ref);  // 0 for rows past the end
       sum += sc[i];
     }
     sum += lane_xor<16>(sum);
@@ -325,6 +326,13 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
   };
+  float finite = 0.0f;  // NaN once a sum is infinite or NaN
+  auto check = [&](const float4& o) {
+    finite = __builtin_fmaf(o.x, 0.0f, finite);
+    finite = __builtin_fmaf(o.y, 0.0f, finite);
+    finite = __builtin_fmaf(o.z, 0.0f, finite);
+    finite = __builtin_fmaf(o.w, 0.0f, finite);
+  };
   float half[8][4];  // dimension 16 n + 8 (g / 2) + e
 #pragma unroll
   for (int e = 0; e < 8; ++e)
@@ -337,16 +345,79 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
         const float4 o = make_float4(add16(half[0][r], half[4][r]), add16(half[1][r], half[5][r]),
                                      add16(half[2][r], half[6][r]), add16(half[3][r], half[7][r]));
         *reinterpret_cast<float4*>(&ored[w][r][16 * n + 8 * (g >> 1) + 4 * (g & 1)]) = o;
+        check(o);
       }
     } else {
       float* dst = &ored[w][4 * (g & 1) + r][16 * n + 8 * (g >> 1)];
-      *reinterpret_cast<float4*>(dst) = make_float4(half[0][r], half[1][r], half[2][r], half[3][r]);
-      *reinterpret_cast<float4*>(dst + 4) = make_float4(half[4][r], half[5][r], half[6][r], half[7][r]);
+      const float4 lo = make_float4(half[0][r], half[1][r], half[2][r], half[3][r]);
+      const float4 hi = make_float4(half[4][r], half[5][r], half[6][r], half[7][r]);
+      *reinterpret_cast<float4*>(dst) = lo;
+      *reinterpret_cast<float4*>(dst + 4) = hi;
+      check(lo);
+      check(hi);
     }
   }
   if (l < NH) {  // lane h < HN holds head h
     om[w][l] = run_m;
     ol[w][l] = run_l;
+  }
+  // Where a value (or a weight) is infinite, the zeros and the signs of the three
+  // parts make NaN of what one product would leave infinite: such a wave takes its
+  // rows again, one by one, each weight whole.
+  if (__any(!(finite == 0.0f))) {
+    float m[NH], den[NH], o[NH][4];  // dimensions 4 l .. + 3
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      m[h] = -INFINITY;
+      den[h] = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[h][e] = 0.0f;
+    }
+    for (r0 = r_begin + kStep * w; r0 < r_end; r0 += kPass)
+      for (int64_t row = r0; row < min(r0 + kStep, r_end); ++row) {
+        const bool cached = row < p.pos;
+        float kf[4], vf[4], ks = 1.0f, vs = 1.0f;
+        if constexpr (I8) {
+          const uint32_t kw = cached ? reinterpret_cast<const uint32_t*>(p.k)[row * (kHd / 4) + l]
+                                     : reinterpret_cast<const uint32_t*>(knew)[l];
+          const uint32_t vw = cached ? reinterpret_cast<const uint32_t*>(p.v)[row * (kHd / 4) + l]
+                                     : reinterpret_cast<const uint32_t*>(vnew)[l];
+          ks = cached ? p.sk[row] : knew_s;
+          vs = cached ? p.sv[row] : vnew_s;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            kf[e] = byte_f(kw, e);
+            vf[e] = byte_f(vw, e);
+          }
+        } else {
+          load_bf16x4(cached ? reinterpret_cast<const uint16_t*>(p.k) + row * kHd + 4 * l
+                             : reinterpret_cast<const uint16_t*>(knew) + 4 * l, kf);
+          load_bf16x4(cached ? reinterpret_cast<const uint16_t*>(p.v) + row * kHd + 4 * l
+                             : reinterpret_cast<const uint16_t*>(vnew) + 4 * l, vf);
+        }
+#pragma unroll
+        for (int h = 0; h < NH; ++h) {
+          float qf[4], dot = 0.0f;
+          load_bf16x4(p.qkv + h * kHd + 4 * l, qf);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dot = __builtin_fmaf(qf[e], kf[e], dot);
+          const float sc = (wave_sum(dot) * ks) * 0.0625f;
+          const float mx = fmaxf(m[h], sc), ref = mx == -INFINITY ? 0.0f : mx;
+          const float corr = expf(m[h] - ref), wt = expf(sc - ref);
+          m[h] = mx;
+          den[h] = den[h] * corr + wt;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[h][e] = __builtin_fmaf(wt * vs, vf[e], o[h][e] * corr);
+        }
+      }
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      *reinterpret_cast<float4*>(&ored[w][h][4 * l]) = make_float4(o[h][0], o[h][1], o[h][2], o[h][3]);
+      if (l == 0) {
+        om[w][h] = m[h];
+        ol[w][h] = den[h];
+      }
+    }
   }
   __syncthreads();
   // ---- the four waves (one without rows has maximum -inf and sums of 0), then
@@ -354,10 +425,11 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
     const float m = fmaxf(fmaxf(om[0][h], om[1][h]), fmaxf(om[2][h], om[3][h]));
+    const float ref = m == -INFINITY ? 0.0f : m;  // no row of weight: sums of 0
     float od = 0.0f, den = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const float f = expf(om[i][h] - m);
+      const float f = expf(om[i][h] - ref);
       od += ored[i][h][tid] * f;
       den += ol[i][h] * f;
     }
