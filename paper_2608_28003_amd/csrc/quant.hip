@@ -616,7 +616,7 @@ __global__ void pack_bf16_kernel(const uint16_t* __restrict__ w, int64_t n, int6
 
 hipError_t launch_col_absmax(const void* x, bool bf16, int64_t rows, int64_t k, float* amax,
                              hipStream_t st) {
-  if (k % 8 == 0) {
+  if (k % 8 == 0 && rows > 4) {  // (1 row 2.6 us on col_absmax_kernel, 2.9 here; 16 rows 3.6 and 3.0)
     // column tiles of about 40 chunks; about two workgroups a CU, each over a
     // contiguous range of rows with at least one unrolled step.  Each ends with an
     // atomic per column, and those of all workgroups meet in a few lines, so the
@@ -689,8 +689,13 @@ hipError_t launch_quant_rows(const void* x, bool bf16, bool mul, int64_t rows, i
   // 8-column chunks while the rows leave CUs idle (one workgroup per row) and a
   // row still fits one workgroup
   const bool narrow = rows_pad <= 256 && kp / 8 <= 1024;
-  if (bf16 && !mul && !narrow && kp / 16 <= 1024) {
-    // many bf16 rows (activations): several rows per workgroup
+  // many bf16 rows (activations): several rows per workgroup.  E4M3 codes there
+  // where the rows are many, or long and more than the chip's CUs (rows x k, one row a
+  // workgroup / here, us: 300 x 640 3.8 / 4.4, x 2560 5.1 / 4.9; 1000 x 1152 5.6 / 6.2,
+  // 1500 x 1152 7.1 / 6.7, 2048 x 640 5.5 / 4.9; 64 x 10240 5.7 / 7.2, 300 x 10240 9.8 / 8.1)
+  const bool many = !f8 || (kp >= 2048 ? rows_pad > 256 : rows_pad >= 1280) ||
+                    quant_rows_per_workgroup(0) != 0;  // 0: no override
+  if (bf16 && !mul && !narrow && many && kp / 16 <= 1024) {
     const int64_t threads = (kp / 16 + 63) / 64 * 64;
     // rows per workgroup, measured at k = 6912 (requantisation of h): 4 from
     // 2048 rows (17.9 against 19.8 us with 2), 2 below (512 rows: 8.3 against
@@ -714,7 +719,11 @@ hipError_t launch_quant_rows(const void* x, bool bf16, bool mul, int64_t rows, i
 #undef W8A8_QROWS
     return hipGetLastError();
   }
-  if (mul && kp <= (int64_t)kWqWaves * kWqUnits * 256) {
+  // few weight rows of some length leave CUs idle here, and the launch ends with its
+  // longest chain (rows x k bf16, one row a workgroup / here, us: 16 x 1152 3.6 / 4.2, x 6912
+  // 4.3 / 6.3; 300 x 640 4.1 / 4.2, E4M3 3.6 / 4.1; 1000 x 640 4.5 / 4.3, x 6912 11.5 / 7.8;
+  // 300 x 208 4.3 / 3.4)
+  if (mul && (rows_pad >= 512 || kp < 512) && kp <= (int64_t)kWqWaves * kWqUnits * 256) {
     // rows a workgroup: 16 store whole fragments; fewer where the row is long
     // (a workgroup of more than 8 waves holds the chip's slots in step) or the
     // rows are few (512 workgroups fill the chip)

@@ -79,3 +79,26 @@ def test_fp8_many_rows(m, k, r):
     got = w8a8.frag_to_rowmajor(qx.cpu().numpy(), m, k).view(np.uint8)
     np.testing.assert_array_equal(s.cpu().numpy(), s_o)
     np.testing.assert_array_equal(got, q_o)
+
+
+# both sides of the row counts from which the tiles and the many-row kernel are taken
+@pytest.mark.parametrize("n,k", [(496, 1152), (512, 1168), (300, 448), (300, 512), (515, 12288), (600, 6912)])
+def test_weight_codes_rule(n, k):
+    test_weight_codes(n, k, "bf16")
+
+
+@pytest.mark.parametrize("m,k", [(1264, 640), (1265, 640), (272, 1920), (257, 2048), (40, 10240), (257, 10240)])
+def test_fp8_act_rule(m, k):
+    print("fp8 act rule", m, k, flush=True)
+    rng = np.random.default_rng(m + k)
+    x = synth.to_bf16_bits(rng.standard_normal((m, k)).astype(np.float32))
+    delta = np.exp(rng.uniform(-2, 2, k)).astype(np.float32)
+    q_o, s_o = oracle.quantize_act_fp8(x, delta)
+    qx, s = w8a8.fp8_quantize_act(dev(x), dev(delta))
+    np.testing.assert_array_equal(s.cpu().numpy(), s_o)
+    np.testing.assert_array_equal(w8a8.frag_to_rowmajor(qx.cpu().numpy(), m, k).view(np.uint8), q_o)
+
+
+@pytest.mark.parametrize("rows,k", [(4, 1152), (5, 1152), (4, 8), (5, 10240)])
+def test_col_absmax_rule(rows, k):
+    test_col_absmax(rows, k)
