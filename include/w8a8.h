@@ -336,7 +336,10 @@ w8a8_status w8a8_bf16_ffn_gate_up(const w8a8_bf16_ffn_desc* desc, const void* x,
                                   void* h, w8a8_stream_t stream);
 
 /* bf16 FFN block: h = bf16(gelu_tanh(g) * u) with g, u the fp32 accumulators,
-   y = bf16(h W_down^T).  ws: w8a8_bf16_ffn_workspace_bytes(m, d, f). */
+   y = bf16(h W_down^T).  ws: w8a8_bf16_ffn_workspace_bytes(m, d, f).  A smaller
+   one is taken down to the room of h in rows (2 m f bytes, rounded up to 256,
+   and the down projection's partial sums where the plan has them): the call is
+   slower then and gives the same bits. */
 w8a8_status w8a8_bf16_ffn(const w8a8_bf16_ffn_desc* desc, const void* x, int64_t m,
                           void* y, void* ws, size_t ws_bytes, w8a8_stream_t stream);
 

@@ -722,16 +722,25 @@ bool bf16_x_packed(int64_t m, int64_t d, int64_t f) {
          packs(plan_gemm(m, f, d, DT_BF16, true, false));
 }
 
-struct Bf16FfnWs {
-  size_t h, gemm_dn, x, total;
+// The block's two plans and its workspace.  The plans depend on the shape alone;
+// with `pack` the packed activations have their room (whole fragments of h: up to
+// 15 more rows; x a copy), without it they stay in rows.  Either way the same
+// kernels add in the same order: the workspace changes the time, not the bits.
+struct Bf16Ffn {
+  Plan gu, dn;
+  bool h_packed, x_packed;
+  size_t gemm_dn, x, total;  // offsets; h stands first
 };
-Bf16FfnWs bf16_ffn_ws(int64_t m, int64_t d, int64_t f, bool packed, bool x_packed = false) {
-  Bf16FfnWs w;
-  Plan pd = plan_gemm(m, d, f, DT_BF16, false, !packed);
-  w.h = 0;
-  w.gemm_dn = align256(packed ? w8a8_packed_bf16_bytes(m, f) : (size_t)m * f * 2);
-  w.x = w.gemm_dn + plan_ws_bytes(pd, m, d);
-  w.total = w.x + (x_packed ? align256(w8a8_packed_bf16_bytes(m, d)) : 0);
+Bf16Ffn bf16_ffn_plan(int64_t m, int64_t d, int64_t f, bool pack) {
+  Bf16Ffn w;
+  const bool hp = bf16_h_packed(m, d, f), xp = hp && bf16_x_packed(m, d, f);
+  w.gu = plan_gemm(m, f, d, DT_BF16, true, !xp);
+  w.dn = plan_gemm(m, d, f, DT_BF16, false, !hp);
+  w.h_packed = hp && pack;
+  w.x_packed = xp && pack;
+  w.gemm_dn = align256(w.h_packed ? w8a8_packed_bf16_bytes(m, f) : (size_t)m * f * 2);
+  w.x = w.gemm_dn + plan_ws_bytes(w.dn, m, d);
+  w.total = w.x + (w.x_packed ? align256(w8a8_packed_bf16_bytes(m, d)) : 0);
   return w;
 }
 
@@ -898,23 +907,17 @@ w8a8_status bf16_linear_impl(const void* x, int64_t m, const void* wp, int64_t n
 
 w8a8_status bf16_ffn_impl(const w8a8_bf16_ffn_desc* d, const void* x, int64_t m, void* y,
                           void* ws, size_t ws_bytes, hipStream_t st) {
-  // whole fragments of h need up to 15 more rows than its m, a packed x room of
-  // its own: a smaller workspace keeps the one and the other in rows
-  const bool packed = bf16_h_packed(m, d->d, d->f) && ws_bytes >= bf16_ffn_ws(m, d->d, d->f, true).total;
-  const bool xp = packed && bf16_x_packed(m, d->d, d->f) &&
-                  ws_bytes >= bf16_ffn_ws(m, d->d, d->f, true, true).total;
-  Bf16FfnWs w = bf16_ffn_ws(m, d->d, d->f, packed, xp);
+  Bf16Ffn w = bf16_ffn_plan(m, d->d, d->f, true);
+  if (ws_bytes < w.total) w = bf16_ffn_plan(m, d->d, d->f, false);
   char* base = (char*)ws;
-  if (xp) {
+  if (w.x_packed) {
     CHECK(hip_check(launch_pack_bf16(x, m, d->d, base + w.x, st), "pack_bf16"));
     x = base + w.x;
   }
-  Plan pg = plan_gemm(m, d->f, d->d, DT_BF16, true, !xp);
-  CHECK(run_gemm(pg, DT_BF16, EPI_GLU, x, d->d, m, d->wp_gate, d->wp_up, d->f, d->d, nullptr, nullptr,
-                 nullptr, base + w.h, d->f, nullptr, st, QLoad(), xp, packed));
-  Plan pd = plan_gemm(m, d->d, d->f, DT_BF16, false, !packed);
-  return run_gemm(pd, DT_BF16, EPI_BF16, base + w.h, d->f, m, d->wp_down, nullptr, d->d, d->f,
-                  nullptr, nullptr, nullptr, y, d->d, base + w.gemm_dn, st, QLoad(), packed);
+  CHECK(run_gemm(w.gu, DT_BF16, EPI_GLU, x, d->d, m, d->wp_gate, d->wp_up, d->f, d->d, nullptr, nullptr,
+                 nullptr, base, d->f, nullptr, st, QLoad(), w.x_packed, w.h_packed));
+  return run_gemm(w.dn, DT_BF16, EPI_BF16, base, d->f, m, d->wp_down, nullptr, d->d, d->f,
+                  nullptr, nullptr, nullptr, y, d->d, base + w.gemm_dn, st, QLoad(), w.h_packed);
 }
 
 }  // namespace
@@ -945,9 +948,7 @@ size_t w8a8_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
 
 size_t w8a8_bf16_ffn_workspace_bytes(int64_t m, int64_t d, int64_t f) {
   if (m < 1 || d < 1 || f < 1) return 0;
-  const size_t rows = bf16_ffn_ws(m, d, f, false).total;
-  if (!bf16_h_packed(m, d, f)) return rows;
-  return std::max(rows, bf16_ffn_ws(m, d, f, true, bf16_x_packed(m, d, f)).total);
+  return bf16_ffn_plan(m, d, f, true).total;
 }
 
 size_t w8a8_bf16_linear_workspace_bytes(int64_t m, int64_t n, int64_t k) {
@@ -1435,7 +1436,7 @@ w8a8_status w8a8_bf16_ffn(const w8a8_bf16_ffn_desc* desc, const void* x, int64_t
   CHECK_PTR(y);
   CHECK_PTR(ws);
   REQUIRE(m >= 1, W8A8_EINVAL, "m < 1");
-  REQUIRE(ws_bytes >= bf16_ffn_ws(m, desc->d, desc->f, false).total, W8A8_EWORKSPACE,
+  REQUIRE(ws_bytes >= bf16_ffn_plan(m, desc->d, desc->f, false).total, W8A8_EWORKSPACE,
           "workspace too small");
   return bf16_ffn_impl(desc, x, m, y, ws, ws_bytes, S(stream));
 }
