@@ -44,7 +44,7 @@ hipStream_t S(w8a8_stream_t s) { return reinterpret_cast<hipStream_t>(s); }
 
 struct Plan {
   int dt = DT_I8;       // operand type the plan was made for
-  bool stream = false;  // streaming kernel (M <= 128) or tiled kernel
+  bool stream = false;  // streaming kernel (M <= 32) or tiled kernel
   int tile = TILE_128x128;
   int mb = 1;           // streaming: 16-row blocks of A
   int nw = 1, wk = 1;   // streaming: waves per workgroup, waves splitting K
@@ -151,17 +151,16 @@ int64_t tiles_of(int tile, int64_t m, int64_t n) {
   return ceil_div(m, bm) * ceil_div(n, bn);
 }
 
-// Streaming plan for M <= 128, or false if the A panel cannot fit in LDS.
+// Streaming plan for M <= 32, or false if the A panel cannot fit in LDS.
 bool plan_stream(Plan& p, int64_t m, int64_t n, int64_t kb, bool glu, bool f8) {
   const int64_t kstep = f8 ? 2 : 1;  // FP8: K chunks of whole 128-deep MFMA steps
   const int64_t nbc = ceil_div(n, 16);
   const int64_t lds_kb = 158;  // dynamic LDS per workgroup, KiB (one fragment = 1 KiB); the
                                // kernel's static LDS (scales, reduction scratch) takes the rest
-  p.mb = m <= 16 ? 1 : (m <= 32 ? 2 : (m <= 64 ? 4 : 8));
+  p.mb = m <= 16 ? 1 : 2;
   auto lds = [&](int64_t kchunk, int wk) { return p.mb * kchunk + (wk - 1) * (glu ? 2 : 1) * p.mb; };
   if (glu) {  // gate/up pair: no K split across workgroups (the epilogue needs full sums)
     for (int wk : {4, 2, 1}) {
-      if (wk == 4 && p.mb > 4) continue;  // 4-wave K split spills at MB = 8
       if (lds(kb, wk) <= lds_kb) {
         p.nw = p.wk = wk;
         p.splits = 1;
@@ -251,10 +250,10 @@ double kwave_us(const KwTile& t, int64_t m, int64_t n, int64_t row_bytes, bool g
                 int splits = 1) {
   const int64_t bn = glu ? t.bn / 2 : t.bn;
   const double per_cu = (double)ceil_div(ceil_div(m, t.bm) * ceil_div(n, bn) * splits, 256);
-  const double kib = ((a_rows ? 3.0 : 1.0) * t.bm + t.bn) * (double)row_bytes / splits;
-  if (glu) return 4.9 + per_cu * (1.25e-5 * kib + 2.0e-4 * t.bm * t.bn);
+  const double bytes = ((a_rows ? 3.0 : 1.0) * t.bm + t.bn) * (double)row_bytes / splits;
+  if (glu) return 4.9 + per_cu * (1.25e-5 * bytes + 2.0e-4 * t.bm * t.bn);
   const bool alone = t.waves * t.bm * t.bn * 4 > 80 * 1024;
-  return 2.6 + (alone ? 1.0 : t.waves > 8 ? 0.5 : 0.0) + per_cu * (1.4e-5 * kib + 1.2e-4 * t.bm * t.bn);
+  return 2.6 + (alone ? 1.0 : t.waves > 8 ? 0.5 : 0.0) + per_cu * (1.4e-5 * bytes + 1.2e-4 * t.bm * t.bn);
 }
 
 // A step of the ring kernel costs a fixed part and one per column block, its

@@ -446,7 +446,7 @@ __global__ __launch_bounds__(64 * NW, MINB) void gemm_tile_kernel(GemmParams p) 
 
 // ------------------------------------------------------------------ streaming kernel
 
-// Skinny GEMM, M <= 16 * MB rows (MB <= 8), for decode and small prefill
+// Skinny GEMM, M <= 16 * MB rows (MB = 1 or 2), for decode and small prefill
 // batches where the weights dominate the traffic.  The workgroup has NW waves.
 // With WK == 1 every wave walks its own output column blocks of 16 (the wide
 // lm_head); with WK == NW all waves share one column block and split its K
@@ -934,16 +934,13 @@ static hipError_t stream_launch(const GemmParams& p, int nbpb, hipStream_t st) {
 }
 
 // Instantiated wave layouts: 16-wave workgroups only for MB == 1 (at 16 waves a
-// wave has 128 registers, too few for larger MB), 4 waves sharing K only where
-// the accumulators still fit without spilling.
+// wave has 128 registers, too few for two row blocks).
 template <int DT, int MB, int EPI>
 static hipError_t stream_waves(int nw, int wk, const GemmParams& p, int nbpb, hipStream_t st) {
   if (nw == 1 && wk == 1) return stream_launch<DT, MB, EPI, 1, 1>(p, nbpb, st);
   if (nw == 4 && wk == 1) return stream_launch<DT, MB, EPI, 4, 1>(p, nbpb, st);
   if (nw == 2 && wk == 2) return stream_launch<DT, MB, EPI, 2, 2>(p, nbpb, st);
-  if constexpr (MB <= 4 || EPI != EPI_GLU) {
-    if (nw == 4 && wk == 4) return stream_launch<DT, MB, EPI, 4, 4>(p, nbpb, st);
-  }
+  if (nw == 4 && wk == 4) return stream_launch<DT, MB, EPI, 4, 4>(p, nbpb, st);
   if constexpr (MB == 1 && EPI != EPI_GLU) {  // the gated 16-wave variant would spill
     if (nw == 16 && wk == 16) return stream_launch<DT, MB, EPI, 16, 16>(p, nbpb, st);
   }
@@ -955,10 +952,6 @@ static hipError_t stream_mb(int mb, int nw, int wk, const GemmParams& p, int nbp
   switch (mb) {
     case 1: return stream_waves<DT, 1, EPI>(nw, wk, p, nbpb, st);
     case 2: return stream_waves<DT, 2, EPI>(nw, wk, p, nbpb, st);
-    case 4: return stream_waves<DT, 4, EPI>(nw, wk, p, nbpb, st);
-    case 8:
-      if constexpr (DT != DT_F8) return stream_waves<DT, 8, EPI>(nw, wk, p, nbpb, st);
-      return hipErrorInvalidValue;
     default: return hipErrorInvalidValue;
   }
 }

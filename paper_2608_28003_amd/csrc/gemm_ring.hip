@@ -104,7 +104,7 @@ __device__ __forceinline__ void ring_body(const GemmParams& p, v4i* lds, int wav
   constexpr bool GLU = R::GLU, BF16 = R::BF16;
   constexpr int KP = frags_per_mma<DT>();
   constexpr int TH = GLU ? TN / 2 : TN;
-  constexpr int PF = R::PF, NF = R::NF, NB = R::NB;
+  constexpr int PF = R::PF, NB = R::NB;
   const int wm = wave & 3;
   const int c0 = wave < 4 ? 0 : (GLU ? TNA / 2 : TNA);  // this wave's first column block
   float* sc = reinterpret_cast<float*>(lds + S * R::PIECES * 64);  // R::SETS sets of scales

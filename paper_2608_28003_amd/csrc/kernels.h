@@ -100,7 +100,8 @@ enum TileCfg {
                                // four stages, 96 KiB of LDS (1 per CU)
   TILE_256x128_W4 = 17,        // 4 waves of 128 x 64, three stages, 72 KiB of LDS
                                // (2 per CU)
-  // K-wave kernel (gemm_kwave.hip): 4 waves, or 8 (_W8), each over the whole tile
+  // K-wave kernel (gemm_kwave.hip): every wave over the whole tile; 4 waves, 8 in the
+  // _W8 tiles and in the plain 16x32 and 16x64, 16 in the _W16 tile
   TILE_KW_64x144 = 32,
   TILE_KW_64x96 = 33,
   TILE_KW_64x64 = 34,
@@ -148,18 +149,19 @@ hipError_t launch_pack_bf16(const void* w, int64_t n, int64_t k, void* wp, hipSt
 int device_cus();
 // tiled MFMA GEMM (any M); `tile` picks the block shape
 hipError_t launch_gemm_tile(int dt, int epi, int tile, const GemmParams& p, hipStream_t st);
-// the K-wave kernel (TILE_KW_*): no K splits over workgroups
+// the K-wave kernel (TILE_KW_*); K splits over workgroups for raw sums only
 constexpr bool tile_is_kwave(int tile) { return tile >= TILE_KW_64x144 && tile <= TILE_KW_16x16_W16; }
 // the persistent ring kernel (TILE_RING_*): one workgroup on each of `cus` CUs
 constexpr bool tile_is_ring(int tile) { return tile >= TILE_RING_256 && tile <= TILE_RING_128; }
 hipError_t launch_gemm_ring(int dt, int epi, int tile, const GemmParams& p, int cus, hipStream_t st);
 hipError_t launch_gemm_kwave(int dt, int epi, int tile, const GemmParams& p, hipStream_t st);
-// streaming MFMA GEMM for M <= 128: weights streamed from HBM, A staged in
-// LDS; nw waves per workgroup, wk of them splitting one column block's K range
 // Largest M * K / 16 a streaming workgroup of nw waves can quantise on load.
 inline int64_t qload_capacity(int nw) { return (int64_t)64 * nw; }
 // Fused layer glue: K splits of the previous layer it can add (loaded up front).
 constexpr int kGlueMaxSplits = 4;
+// streaming MFMA GEMM for M <= 32 (mb: one or two 16-row blocks): weights streamed
+// from HBM, A staged in LDS; nw waves per workgroup, wk of them splitting one
+// column block's K range
 hipError_t launch_gemm_stream(int dt, int epi, int mb, int nw, int wk, const GemmParams& p,
                               int nb_per_block, hipStream_t st);
 size_t gemm_stream_lds_bytes(int mb, int kchunk, int wk, bool glu);
