@@ -274,9 +274,12 @@ def measured_traffic(m):
     except (OSError, AttributeError, ValueError):
         return None
     h = hashlib.sha256()
-    for f in ("gemm.hip", "device.h", "kernels.h", "api.hip"):  # kernels and their plans
-        with open(os.path.join(ROOT, "paper_2608_28003_amd", "csrc", f), "rb") as fh:
-            h.update(fh.read())
+    # the kernels that a plan may choose, and the plans
+    for f in ("gemm.hip", "device.h", "kernels.h", "api.hip", "gemm_kwave.hip", "gemm_ring.hip"):
+        src = os.path.join(ROOT, "paper_2608_28003_amd", "csrc", f)
+        if os.path.exists(src):
+            with open(src, "rb") as fh:
+                h.update(fh.read())
     if rec.get("m") != m or rec.get("source_sha256") != h.hexdigest():
         return None
     return rec["traffic_bytes"]
@@ -343,7 +346,8 @@ def gate_up_roofline(torch, w8a8, int8_layers, x, M, D, F, NL, make_graph, time_
     del g
     ops = 2.0 * M * D * 2 * F
     nbytes = 2 * F * D + 8 * F + 4 * D + 2 * M * D
-    common = {"kernel": "gemm_tile_kernel<int8, GeGLU epilogue> (FFN gate/up)",
+    common = {"kernel": "int8 FFN gate/up GEMM with the GeGLU epilogue (the K-wave, LDS-tile or "
+                        "ring kernel that is planned for m)",
               "avg_launch_us": round(t * 1e6, 3), "ops_per_launch": ops,
               "algorithmic_bytes_per_launch": nbytes, "m": M,
               "int8_tops": round(ops / t / 1e12, 1), "GBs": round(nbytes / t / 1e9, 1)}

@@ -57,3 +57,16 @@ def test_committed_summaries_carry_a_machine_read_record():
         start = text.index("```json\n") + len("```json\n")
         rec = json.loads(text[start:text.index("\n```", start)])
         assert rec["m"] == m and rec["traffic_bytes"] > 0 and len(rec["source_sha256"]) == 64
+
+
+def test_traffic_follows_every_gemm_source(tmp_path, monkeypatch):
+    good = _fake_tree(tmp_path, 2048, sha="0" * 64)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    rec_path = tmp_path / "profiles" / "gate_up_geglu_m2048_hbm_traffic.md"
+    rec_path.write_text(rec_path.read_text().replace("0" * 64, good))
+    assert bench.measured_traffic(2048) == 12345
+    for name in ("gemm_ring.hip", "gemm_kwave.hip"):
+        (tmp_path / "paper_2608_28003_amd" / "csrc" / name).write_text("// another kernel\n")
+        assert bench.measured_traffic(2048) is None, name
+        (tmp_path / "paper_2608_28003_amd" / "csrc" / name).unlink()
+        assert bench.measured_traffic(2048) == 12345
