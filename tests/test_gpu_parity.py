@@ -426,10 +426,8 @@ def test_linear_attention_shapes_bit_exact(m, n, k):
 
 @pytest.mark.parametrize("out_dtype", ["f32", "bf16"])
 def test_linear_wide_tile_both_epilogues_bit_exact(out_dtype):
-    """The 4-wave 256 x 128 tile (the plan from M = 512 on wide outputs) with
-    both dequantising epilogues, ragged in M (600 = 2 * 256 + 88) and N
-    (1000 = 7 * 128 + 104); the planner's own choice at M = 1024, N = 13824
-    is the same tile."""
+    """The 4-wave 256 x 128 tile with both dequantising epilogues, ragged in M
+    (600 = 2 * 256 + 88) and N (1000 = 7 * 128 + 104)."""
     say("linear 4-wave 256 x 128 tile", out_dtype)
     m, n, k = 600, 1000, 1152
     x = act_input(m, k, 4242)
@@ -621,9 +619,9 @@ def lm_full():
 
 @pytest.mark.parametrize("m", [1, 8, 64, 256, 600])
 def test_lm_head_full_vocab_sampled_columns(m, lm_full):
-    """M = 256 takes the 256 x 256 tile, M = 600 the 4-wave 256 x 128 tile
-    with a ragged last row block of 88 (rows beyond the fixture's 64 are
-    scaled and negated copies, so every row block holds distinct rows)."""
+    """M = 256 and 600 take the ring kernel's 256 x 256 tile, M = 600 with a
+    ragged last row block of 88 (rows beyond the fixture's 64 are scaled and
+    negated copies, so every row block holds distinct rows)."""
     say("lm_head full vocab, sampled columns", m)
     cfg, delta, layer = lm_full
     x = cfg["x"]
