@@ -419,9 +419,13 @@ Plan plan_gemm(int64_t m, int64_t n, int64_t k, int dt, bool glu, bool a_rows = 
   // 7.7 us), and up to 32 of row-major bf16 (the same, M = 8: 10.5 against 12.9);
   // up to 32 of very wide outputs with short rows, whose panel leaves room for
   // several workgroups a CU (K = 640, M = 17: 262144 columns 38.9 against 43.0 us,
-  // FP8 38.1 against 47.6; 32000 columns 10.7 against 9.9).
+  // FP8 38.1 against 47.6; 32000 columns 10.7 against 9.9); up to 16 of gated bf16
+  // whose K gives each of the four waves one batch of loads and not much less (the
+  // block, M = 1: d = 1152 18.0 against 18.8 us on K-wave tiles, 1024 13.1 and 13.8;
+  // 640 10.4 both, 256 7.7 and 7.4, 1536, two batches, 19.4 and 18.2).
   if (m <= 32 && !plan_override("NO_STREAM", 0) && plan_stream(p, m, n, kb, glu, f8)) {
-    const bool fits = dt == DT_BF16 ? !glu && a_rows
+    const bool one_batch = glu && a_rows && m <= 16 && kb > 24 && kb <= 36;
+    const bool fits = dt == DT_BF16 ? (!glu && a_rows) || one_batch
                                     : m <= 16 && (wide || m * (k / 16) <= qload_capacity(p.nw) ||
                                                   (f8 && !glu && k >= 4096 && p.splits == 1));
     if (fits || (wide && (m <= 16 || (k <= 640 && n >= 65536)))) {
