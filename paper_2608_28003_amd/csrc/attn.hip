@@ -364,7 +364,7 @@ __global__ __launch_bounds__(256, I8 ? 2 : 1) void attn_decode_kernel(AttnParams
   // Where a value (or a weight) is infinite, the zeros and the signs of the three
   // parts make NaN of what one product would leave infinite: such a wave takes its
   // rows again, one by one, each weight whole.
-  if (__any(!(finite == 0.0f))) {
+  if (__builtin_expect(__any(!(finite == 0.0f)) != 0, 0)) {
     float m[NH], den[NH], o[NH][4];  // dimensions 4 l .. + 3
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
