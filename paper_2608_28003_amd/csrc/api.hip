@@ -371,8 +371,8 @@ double tile_us(const TileCost& t, int64_t m, int64_t n, int64_t k, int dt, int s
 // time is lower by more than the rows' error.  Candidates: the LDS tiles, for
 // very wide outputs (any = true) every tile, and for the long K of few bf16 columns
 // two LDS tiles with K in three parts.  What it takes back (a pass through the
-// linear): bf16 4096 x 640 x 14336 250 -> 129 us, 512 x 8192 x 6912 146 -> 110; FP8
-// 256 x 12288 x 128 14.2 -> 8.6; int8 256 x 16384 x 1152 24.5 -> 18.0.
+// linear): bf16 4096 x 640 x 14336 250 -> 129 us, 512 x 8192 x 6912 146 -> 108; FP8
+// 256 x 12288 x 128 14.2 -> 8.6; int8 256 x 16384 x 1152 24.5 -> 19.9, bf16 38.8 -> 23.2.
 int plan_measured(int pick, int64_t m, int64_t n, int64_t k, int dt, bool any, int* splits) {
   const TileCost* rows = dt == DT_I8 ? kCostI8 : dt == DT_BF16 ? kCostBf16 : kCostF8;
   const int n_rows = (int)(dt == DT_I8     ? sizeof(kCostI8)
